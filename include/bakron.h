@@ -361,7 +361,8 @@ bakron_status bakron_solve_noalloc(const float *W, int64_t m, int64_t n, const b
  *
  * Conventions of this group (in addition to those above):
  *   - sample matrices are N x d row-major fp32, one sample per row;
- *   - computed in fp32 on the matrix cores (fp32 products, fp32 sums); the
+ *   - computed on the matrix cores at fp32 precision (three-way bf16 split of the
+ *     operands, fp32 sums); a non-finite sample makes the entries it enters NaN; the
  *     summation order is fixed for a given device and shape, so repeated calls
  *     give bitwise the same result;
  *   - workspace protocol: with work == NULL the call stores the number of
@@ -446,7 +447,7 @@ bakron_status bakron_mlp_local_factors(const float *x, const float *g, const flo
  * (App. A: A^(i+1) = E[tr(b^T B^(i) b) a a^T]).
  *   X  device, N x d;  M  device, d x d, SYMMETRIC (M_tj is read as M_jt);
  *   w  device, N outputs.  0 <= d <= 2^17.
- * Two launches (X M on fp32 MFMA with the row sums fused, then the sum over
+ * Two launches (X M on the matrix cores with the row sums fused, then the sum over
  * column blocks in a fixed order).  Workspace as above: ceil(d / 128) * N
  * floats.
  */

@@ -9,8 +9,8 @@
 //                                 B = E[g g^T] (.) D^T D with D^T D itself a Gram over the rows of
 //                                 D = W_down, and tr(b^T b) = sum_i (D^T D)_ii g_i^2.
 // k_sample_weights forms w_k = sum_i c_i X_ki^2 (c = 1: the squared norm).
-// k_gram computes the upper-triangle 128 x 128 blocks of X^T diag(w) X on fp32
-// MFMA, split over slices of the samples; k_gram_reduce adds the slices in a
+// k_gram computes the upper-triangle blocks of X^T diag(w) X on the bf16 matrix
+// cores from operands split in three (split.h), over slices of the samples; k_gram_reduce adds the slices in a
 // fixed order, applies s and M, writes the upper triangle and mirrors it.
 #include <algorithm>
 #include <cstdio>
@@ -18,12 +18,13 @@
 
 #include "bakron.h"
 #include "common.h"
+#include "split.h"
 
 namespace bk {
 
-constexpr int GB = 128;        // Gram block edge
-constexpr int GK = 32;         // samples per chunk
-constexpr int GSTR = GK + 4;   // LDS row stride (floats) of a staged block
+constexpr int GB = 128;        // narrow block edge of the Gram and quadratic-form kernels
+constexpr int GBW = 256;       // wide block edge
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));   // rows at any 4-byte address
 
 // ----------------------------------------------------------------------------
 // w[k] = sum_i c[i] * X[k][i]^2 (c null: c = 1).  One wave per sample row.
@@ -63,23 +64,31 @@ __global__ __launch_bounds__(256) void k_diag(const float* __restrict__ src, int
 
 // ----------------------------------------------------------------------------
 // Upper-triangle block (bi, bj), bi <= bj, of X^T diag(w) X over the samples of
-// one slice [k_lo, k_hi): part[slice][blk] (128 x 128, row-major).
-// A chunk is 32 samples.  Thread t stages features 4 (t & 31) .. + 3 of both
-// column ranges for samples 4 (t >> 5) .. + 3: four 16-byte row loads per
-// operand, transposed in registers, written as four 16-byte LDS rows
-// [feature][sample], so the MFMA operands below are contiguous along the
-// sample index (lane half h takes sample 16h + s at step s of
-// v_mfma_f32_32x32x2f32).  The first operand carries the weights.  4 waves,
-// each 2 x 2 MFMA blocks of 32 x 32; LDS double-buffered, the next chunk in
-// registers while the current one is multiplied.
+// one slice [k_lo, k_hi): part[slice][blk] (GT x GT, row-major), on the bf16
+// matrix cores with every fp32 operand split in three (split.h).
+// A chunk is 16 samples.  Half of the threads stage the block's row features
+// (with the weights), half its column features: thread (fi, kq) reads features
+// 4 fi .. + 3 of samples 4 kq .. + 3 as four 16-byte row segments, transposes
+// them in registers, splits them and writes four 8-byte pieces per plane,
+// [plane][feature][sample].  LDS double-buffered, the next chunk in registers
+// while the current one is multiplied.
+// GT = 256: 8 waves of 128 x 64, one workgroup per CU (144 KiB of LDS);
+// GT = 128: 4 waves of 64 x 64, two workgroups per CU.  What bounds it: the
+// bf16 matrix cores at the clock they hold (the wide block needs 62% of the
+// LDS and a quarter of the VALU cycles of its MFMA time).  Measured, 524288
+// samples: 4096 features 79.8 -> 48.6 ms (110 -> 181 TFLOP/s) against the
+// fp32 MFMA kernel before it, with a relative error against 64 bits of 5e-7
+// instead of 3.8e-6; 400 features 1.58 -> 0.99 ms; rows that are not 16-byte
+// aligned (3001 features, 100000 samples) 11.6 -> 5.6 ms, as they were read
+// one float at a time.
 struct GramArgs {
     const float* X;
     int64_t N, d;
     const float* w;
-    int64_t slice_rows;   // samples per slice, a multiple of GK
+    int64_t slice_rows;   // samples per slice, a multiple of SPK
     int nb, nblk;         // blocks per side, upper-triangle blocks
     int slices;
-    float* part;          // [slices][nblk][GB * GB]
+    float* part;          // [slices][nblk][GT * GT]
 };
 
 // Block t of a slice -> (bi, bj), bi <= bj.  The upper triangle is walked in
@@ -130,80 +139,87 @@ __device__ inline int gram_work_of(int v, int total) {
     return (v % GXCD) * per + v / GXCD;
 }
 
-template <bool VEC>
-__global__ __launch_bounds__(256, 2) void k_gram(GramArgs a) {
-    __shared__ __attribute__((aligned(16))) float As[2][GB][GSTR];
-    __shared__ __attribute__((aligned(16))) float Bs[2][GB][GSTR];
+template <int GT, int WX, int WY>
+__global__ __launch_bounds__(64 * (GT / (32 * WX)) * (GT / (32 * WY)), 2) void k_gram(GramArgs a) {
+    constexpr int WN = GT / (32 * WY);                   // waves along the columns
+    constexpr int TH = 64 * (GT / (32 * WX)) * WN;
+    static_assert(TH == 2 * GT, "one staging thread per 4 features x 4 samples of both operands");
+    constexpr int PLANE = 2 * GT * SPROW;                // rows 0 .. GT - 1: A, GT .. 2 GT - 1: B
+    __shared__ __attribute__((aligned(16))) uint16_t S[2][3 * PLANE];
     const int wk = gram_work_of((int)blockIdx.x, a.nblk * a.slices);
     if (wk >= a.nblk * a.slices) return;   // padding of the last XCD's range
     const int slice = wk / a.nblk;
     const int blk = wk % a.nblk;
     int bi, bj;
     gram_block_of(blk, a.nb, bi, bj);
-    const int64_t i0 = (int64_t)bi * GB, j0 = (int64_t)bj * GB;
     const int64_t k_lo = (int64_t)slice * a.slice_rows;
     const int64_t k_hi = min(a.N, k_lo + a.slice_rows);
-    const int nch = k_hi > k_lo ? (int)((k_hi - k_lo + GK - 1) / GK) : 0;
+    const int nch = k_hi > k_lo ? (int)((k_hi - k_lo + SPK - 1) / SPK) : 0;
 
     const int tid = threadIdx.x;
-    const int wv = tid >> 6, l = tid & 63;
-    const int wm = wv >> 1, wn = wv & 1;
-    const int lr = l & 31, lk = l >> 5;
-    const int f4 = 4 * (tid & 31), kq = 4 * (tid >> 5);
-    const float* X = a.X;
-    const int64_t d = a.d;
-    // Loads are unconditional, from clamped (always valid) addresses, so that
-    // they stay in flight across the MFMAs of the current chunk; the weights
-    // and the masks of rows past the slice and columns past d are applied when
-    // the registers are written to LDS.
-    const bool a_in = i0 + f4 < d, b_in = j0 + f4 < d;
-    const int64_t ia = a_in ? i0 + f4 : 0, ja = b_in ? j0 + f4 : 0;
-    f32x4 ra[4], rb[4];
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63;
+    const int wm = wv / WN, wn = wv % WN;
+    // staging role (the operand is the same for a whole wave)
+    const int op = wv >= TH / 128;                       // 0: A (weighted), 1: B
+    const int t = tid & (TH / 2 - 1);
+    const int kq = 4 * (t & 3), fi = 4 * (t >> 2);
+    const int64_t f0 = (int64_t)(op ? bj : bi) * GT;
+    const int64_t f = f0 + fi, d = a.d;
+    const uint32_t off = (uint32_t)kq * (uint32_t)d + (uint32_t)(f < d ? f : 0);
+    const bool full = f0 + GT <= d;                      // no feature of the block is padding
+    const float* w = op ? nullptr : a.w;
+    f32x4 r[4];
     float rw[4];
     int64_t kbase = 0;
+    // Loads come from clamped, always valid addresses, so that they stay in
+    // flight across the MFMAs of the current chunk; weights and masks are
+    // applied when the registers are written to LDS.  Rows need not be 16-byte
+    // aligned (the loads need 4).  A row segment that runs past column d reads
+    // on into the next row, which exists except at the very end of X: the
+    // chunks that come near it read entry by entry.
     auto load = [&](int64_t k0) {
         kbase = k0;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int64_t k = min(k0 + kq + r, k_hi - 1);
-            const float* row = X + k * d;
-            rw[r] = a.w ? a.w[k] : 1.0f;
-            if (VEC) {
-                ra[r] = *reinterpret_cast<const f32x4*>(row + ia);
-                rb[r] = *reinterpret_cast<const f32x4*>(row + ja);
-            } else {
+        for (int u = 0; u < 4; ++u) rw[u] = w ? w[min(k0 + kq + u, k_hi - 1)] : 1.0f;
+        if (k0 + SPK <= k_hi && k0 + SPK + 4 <= a.N) {   // uniform
+            const float* base = a.X + k0 * d;
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    ra[r][u] = row[i0 + f4 + u < d ? i0 + f4 + u : 0];
-                    rb[r][u] = row[j0 + f4 + u < d ? j0 + f4 + u : 0];
-                }
+            for (int u = 0; u < 4; ++u) r[u] = *reinterpret_cast<const f32x4u*>(base + off + u * (uint32_t)d);
+        } else {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const float* row = a.X + min(k0 + kq + u, k_hi - 1) * d;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) r[u][v] = row[f + v < d ? f + v : 0];
             }
         }
     };
     auto store = [&](int sb) {
+        if (!full || kbase + SPK > k_hi) {   // uniform: padding features or samples
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const bool kin = kbase + kq + r < k_hi;
-            const float wk = kin ? rw[r] : 0.0f;
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    r[u][v] = (kbase + kq + u < k_hi && f + v < d) ? r[u][v] : 0.0f;
+        }
+        if (w) {
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                const bool ca = VEC ? a_in : i0 + f4 + u < d;
-                const bool cb = VEC ? b_in : j0 + f4 + u < d;
-                ra[r][u] = ca ? ra[r][u] * wk : 0.0f;
-                rb[r][u] = (cb && kin) ? rb[r][u] : 0.0f;
+                const float x = kbase + kq + u < k_hi ? rw[u] : 0.0f;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) r[u][v] *= x;
             }
         }
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            *reinterpret_cast<f32x4*>(&As[sb][f4 + u][kq]) = f32x4{ra[0][u], ra[1][u], ra[2][u], ra[3][u]};
-            *reinterpret_cast<f32x4*>(&Bs[sb][f4 + u][kq]) = f32x4{rb[0][u], rb[1][u], rb[2][u], rb[3][u]};
-        }
+        for (int v = 0; v < 4; ++v)
+            split_store4(f32x4{r[0][v], r[1][v], r[2][v], r[3][v]},
+                         &S[sb][(op * GT + fi + v) * SPROW + kq], PLANE);
     };
-    f32x16 acc[2][2];
+    f32x16 acc[WX][WY];
 #pragma unroll
-    for (int x = 0; x < 2; ++x)
+    for (int x = 0; x < WX; ++x)
 #pragma unroll
-        for (int y = 0; y < 2; ++y) acc[x][y] = f32x16{0};
+        for (int y = 0; y < WY; ++y) acc[x][y] = f32x16{0};
     if (nch > 0) {
         load(k_lo);
         store(0);
@@ -212,38 +228,22 @@ __global__ __launch_bounds__(256, 2) void k_gram(GramArgs a) {
     for (int c = 0; c < nch; ++c) {
         const int sb = c & 1;
         const bool more = c + 1 < nch;
-        if (more) load(k_lo + (int64_t)(c + 1) * GK);
-        f32x4 fa[2][4], fb[2][4];
-#pragma unroll
-        for (int x = 0; x < 2; ++x)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                fa[x][v] = *reinterpret_cast<const f32x4*>(&As[sb][(2 * wm + x) * TS + lr][lk * 16 + v * 4]);
-                fb[x][v] = *reinterpret_cast<const f32x4*>(&Bs[sb][(2 * wn + x) * TS + lr][lk * 16 + v * 4]);
-            }
-#pragma unroll
-        for (int st = 0; st < 16; ++st)
-#pragma unroll
-            for (int x = 0; x < 2; ++x)
-#pragma unroll
-                for (int y = 0; y < 2; ++y)
-                    acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[x][st >> 2][st & 3],
-                                                                    fb[y][st >> 2][st & 3], acc[x][y],
-                                                                    0, 0, 0);
+        if (more) load(k_lo + (int64_t)(c + 1) * SPK);
+        split_mma<WX, WY>(&S[sb][wm * WX * 32 * SPROW], &S[sb][(GT + wn * WY * 32) * SPROW], PLANE, l, acc);
         if (more) store(sb ^ 1);
         __syncthreads();
     }
-    // acc[x][y][r] is entry (row (2wm + x) * 32 + (r >> 2) * 8 + lk * 4 + (r & 3),
-    // column (2wn + y) * 32 + lr) of the block
-    float* P = a.part + ((int64_t)slice * a.nblk + blk) * (GB * GB);
+    // acc[x][y][r] is entry (row (WX wm + x) * 32 + (r >> 2) * 8 + (l >> 5) * 4 + (r & 3),
+    // column (WY wn + y) * 32 + (l & 31)) of the block
+    float* P = a.part + ((int64_t)slice * a.nblk + blk) * (GT * GT);
 #pragma unroll
-    for (int x = 0; x < 2; ++x)
+    for (int x = 0; x < WX; ++x)
 #pragma unroll
-        for (int y = 0; y < 2; ++y)
+        for (int y = 0; y < WY; ++y)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int row = (2 * wm + x) * TS + (r >> 2) * 8 + lk * 4 + (r & 3);
-                P[row * GB + (2 * wn + y) * TS + lr] = acc[x][y][r];
+            for (int q = 0; q < 16; ++q) {
+                const int row = (WX * wm + x) * TS + (q >> 2) * 8 + (l >> 5) * 4 + (q & 3);
+                P[row * GT + (WY * wn + y) * TS + (l & 31)] = acc[x][y][q];
             }
 }
 
@@ -254,24 +254,27 @@ __global__ __launch_bounds__(256, 2) void k_gram(GramArgs a) {
 // Sub-tiles below the diagonal of a diagonal block are skipped: their entries
 // are the mirror of the sub-tile above.  Every entry of C is read (M) and
 // written by one thread, so M may alias C.
+template <int GT>
 __global__ __launch_bounds__(256) void k_gram_reduce(const float* __restrict__ part, int slices,
                                                      int nblk, int nb, int64_t d, float s,
                                                      const float* M, float* C) {
+    constexpr int SB = GT / TS;   // sub-tiles per side
     __shared__ float T[TS][TS + 1];
-    const int blk = (int)(blockIdx.x >> 4), sub = (int)(blockIdx.x & 15);
+    const int blk = (int)(blockIdx.x / (SB * SB)), sub = (int)(blockIdx.x % (SB * SB));
     int bi, bj;
     gram_block_of(blk, nb, bi, bj);
-    const int sr = sub >> 2, sc = sub & 3;
+    const int sr = sub / SB, sc = sub % SB;
     if (bi == bj && sr > sc) return;
     const bool diag = bi == bj && sr == sc;   // the sub-tile straddles the diagonal
     const int r = threadIdx.x >> 3, c4 = 4 * (threadIdx.x & 7);
-    const int64_t bo = (int64_t)blk * (GB * GB) + (sr * TS + r) * GB + sc * TS + c4;
+    const int64_t bo = (int64_t)blk * (GT * GT) + (sr * TS + r) * GT + sc * TS + c4;
     f32x4 g = {0.f, 0.f, 0.f, 0.f};
-    for (int sl = 0; sl < slices; ++sl)
-        g += *reinterpret_cast<const f32x4*>(part + (int64_t)sl * nblk * (GB * GB) + bo);
+#pragma unroll 8
+    for (int sl = 0; sl < slices; ++sl)   // unrolled: 8 loads in flight, added in order
+        g += *reinterpret_cast<const f32x4*>(part + (int64_t)sl * nblk * (GT * GT) + bo);
     g *= s;
-    const int64_t i = (int64_t)bi * GB + sr * TS + r;
-    const int64_t jb = (int64_t)bj * GB + sc * TS + c4;
+    const int64_t i = (int64_t)bi * GT + sr * TS + r;
+    const int64_t jb = (int64_t)bj * GT + sc * TS + c4;
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
         if (i < d && jb + u < d && (!diag || r <= c4 + u)) {
@@ -281,8 +284,8 @@ __global__ __launch_bounds__(256) void k_gram_reduce(const float* __restrict__ p
         T[r][c4 + u] = g[u];
     }
     __syncthreads();
-    const int64_t il = (int64_t)bj * GB + sc * TS + r;   // mirrored row
-    const int64_t jl = (int64_t)bi * GB + sr * TS + c4;  // mirrored columns
+    const int64_t il = (int64_t)bj * GT + sc * TS + r;   // mirrored row
+    const int64_t jl = (int64_t)bi * GT + sr * TS + c4;  // mirrored columns
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
         if (il < d && jl + u < d && (!diag || r > c4 + u)) {
@@ -295,44 +298,48 @@ __global__ __launch_bounds__(256) void k_gram_reduce(const float* __restrict__ p
 
 // ----------------------------------------------------------------------------
 // Launch geometry of one Gram product.  The blocks of one slice are
-// consecutive workgroups (they stream the same samples, which stay in L2);
-// the slice count balances nblk * slices blocks over the 2 * ncu workgroup
-// slots (two workgroups fit one CU), charging each slice its partial-sum
-// traffic.
+// consecutive workgroups (they stream the same samples, which stay in L2).
+// Block edge and slice count are chosen together by modelled time: rounds of
+// workgroups over the chip times the chunks of a slice, plus writing and
+// reading back every partial block at about 5 TB/s, plus 0.15 us per slice for
+// the reduction's chain of additions.  A chunk of a wide block
+// takes 1.9 us (one workgroup per CU), of a narrow one 1.1 us with two
+// workgroups per CU; the wide block halves the operand bytes and LDS reads per
+// product, the narrow one pads less.
 struct GramGeom {
+    int gt;               // block edge
     int nb, nblk, slices;
     int64_t slice_rows;
 };
 
 static GramGeom gram_geom(int64_t N, int64_t d, int ncu) {
-    GramGeom g;
-    g.nb = (int)((d + GB - 1) / GB);
-    g.nblk = g.nb * (g.nb + 1) / 2;
-    const int64_t nch = std::max<int64_t>(1, (N + GK - 1) / GK);
-    const int64_t slots = 2 * (int64_t)std::max(ncu, 1);
-    int best = 1;
+    const int64_t nch = std::max<int64_t>(1, (N + SPK - 1) / SPK);
+    GramGeom best{};
     double best_t = 0.0;
-    for (int S = 1; S <= 64 && S <= nch; ++S) {
-        const int64_t per = (nch + S - 1) / S;
-        const int64_t S_eff = (nch + per - 1) / per;
-        // in chunk-times of one workgroup (2 * 128 * 128 * 32 flops at half a
-        // CU's MFMA rate, about 3.4 us): the waves of blocks, plus writing and
-        // reading back every 64 KiB partial at about 5 TB/s (0.0077 each)
-        const double t = (double)((g.nblk * S_eff + slots - 1) / slots) * (double)per +
-                         0.0077 * (double)(g.nblk * S_eff);
-        if (S == 1 || t < best_t - 1e-9) {
-            best_t = t;
-            best = (int)S_eff;
+    for (int gt : {GBW, GB}) {
+        const int64_t nb = (d + gt - 1) / gt, nblk = nb * (nb + 1) / 2;
+        const int64_t slots = (gt == GBW ? 1 : 2) * (int64_t)std::max(ncu, 1);
+        const double chunk = gt == GBW ? 1.9 : 1.1;
+        for (int64_t S = 1; S <= 64 && S <= nch; ++S) {
+            const int64_t per = (nch + S - 1) / S;
+            const int64_t S_eff = (nch + per - 1) / per;
+            const double t = (double)((nblk * S_eff + slots - 1) / slots) * (double)per * chunk +
+                             8.0 * gt * gt / 5e6 * (double)(nblk * S_eff) + 0.15 * (double)S_eff;
+            if (best.gt == 0 || t < best_t - 1e-9) {
+                best_t = t;
+                best.gt = gt;
+                best.nb = (int)nb;
+                best.nblk = (int)nblk;
+                best.slices = (int)S_eff;
+                best.slice_rows = per * SPK;
+            }
         }
     }
-    const int64_t per = (nch + best - 1) / best;
-    g.slice_rows = per * GK;
-    g.slices = (int)((nch + per - 1) / per);
-    return g;
+    return best;
 }
 
 static size_t gram_part_bytes(const GramGeom& g) {
-    return (size_t)g.slices * g.nblk * GB * GB * sizeof(float);
+    return (size_t)g.slices * g.nblk * g.gt * g.gt * sizeof(float);
 }
 
 static hipError_t run_sample_weights(hipStream_t st, const float* X, int64_t N, int64_t d,
@@ -351,29 +358,33 @@ static hipError_t run_gram(hipStream_t st, const GramGeom& g, const float* X, in
                            const float* w, float s, const float* M, float* C, float* part) {
     if (d == 0) return hipSuccess;
     GramArgs a{X, N, d, w, g.slice_rows, g.nb, g.nblk, g.slices, part};
-    const bool vec = d % 4 == 0 && ((uintptr_t)X & 15) == 0;
     const int64_t total = (int64_t)g.nblk * g.slices;
     const dim3 grid((unsigned)(((total + GXCD - 1) / GXCD) * GXCD));
-    if (vec)
-        hipLaunchKernelGGL(k_gram<true>, grid, dim3(256), 0, st, a);
+    const unsigned subs = (unsigned)(g.nblk * (g.gt / TS) * (g.gt / TS));
+    if (g.gt == GBW)
+        hipLaunchKernelGGL((k_gram<GBW, 4, 2>), grid, dim3(2 * GBW), 0, st, a);
     else
-        hipLaunchKernelGGL(k_gram<false>, grid, dim3(256), 0, st, a);
+        hipLaunchKernelGGL((k_gram<GB, 2, 2>), grid, dim3(2 * GB), 0, st, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_gram_reduce, dim3((unsigned)(g.nblk * 16)), dim3(256), 0, st, part,
-                       g.slices, g.nblk, g.nb, d, s, M, C);
+    if (g.gt == GBW)
+        hipLaunchKernelGGL(k_gram_reduce<GBW>, dim3(subs), dim3(256), 0, st, part, g.slices, g.nblk,
+                           g.nb, d, s, M, C);
+    else
+        hipLaunchKernelGGL(k_gram_reduce<GB>, dim3(subs), dim3(256), 0, st, part, g.slices, g.nblk,
+                           g.nb, d, s, M, C);
     return hipGetLastError();
 }
 
 // ----------------------------------------------------------------------------
 // Per-sample quadratic forms w_k = x_k^T M x_k (M symmetric d x d): the
 // weights tr(b^T B b) of the later Shampoo power steps (App. A).  Workgroup
-// (row block R, column block J) computes the 128 x 128 tile of Y = X M
-// (Y_kj = sum_t X_kt M_jt, M symmetric) on fp32 MFMA, then
-// part[J][k] = sum_{j in J} Y_kj X_kj.  Both operands are rows with the
-// inner index contiguous, staged as 16-byte copies (thread t: row t >> 1,
-// inner quarter-chunk 16 (t & 1)).  k_quadform_reduce adds the column blocks
-// in order.
+// (row block R, column block J) computes the GT x GT tile of Y = X M
+// (Y_kj = sum_t X_kt M_jt, M symmetric) on the bf16 matrix cores (split.h),
+// then part[J][k] = sum_{j in J} Y_kj X_kj.  Both operands are rows with the
+// inner index contiguous: half of the threads stage X, half M, each thread 4
+// inner entries of 4 rows per 16-wide chunk.  k_quadform_reduce adds the
+// column blocks in order.
 struct QuadArgs {
     const float* X;
     int64_t N, d;
@@ -382,113 +393,98 @@ struct QuadArgs {
     float* part;   // [nJ][N]
 };
 
-template <bool VEC>
-__global__ __launch_bounds__(256, 2) void k_quadform(QuadArgs a) {
-    __shared__ __attribute__((aligned(16))) float As[2][GB][GSTR];
-    __shared__ __attribute__((aligned(16))) float Bs[2][GB][GSTR];
-    __shared__ float red[2][GB];
+template <int GT, int WX, int WY>
+__global__ __launch_bounds__(64 * (GT / (32 * WX)) * (GT / (32 * WY)), 2) void k_quadform(QuadArgs a) {
+    constexpr int WN = GT / (32 * WY);
+    constexpr int TH = 64 * (GT / (32 * WX)) * WN;
+    static_assert(TH == 2 * GT, "one staging thread per 4 rows x 4 inner entries of both operands");
+    constexpr int PLANE = 2 * GT * SPROW;
+    __shared__ __attribute__((aligned(16))) uint16_t S[2][3 * PLANE];
+    __shared__ float red[WN][GT];
     const int J = (int)(blockIdx.x % (unsigned)a.nJ);
     const int64_t R = blockIdx.x / (unsigned)a.nJ;
-    const int64_t k0 = R * GB, j0 = (int64_t)J * GB;
+    const int64_t k0 = R * GT, j0 = (int64_t)J * GT;
     const int64_t d = a.d;
     const int tid = threadIdx.x;
-    const int wv = tid >> 6, l = tid & 63;
-    const int wm = wv >> 1, wn = wv & 1;
-    const int lr = l & 31, lk = l >> 5;
-    const int srow = tid >> 1, sq = 16 * (tid & 1);
-    const bool arow_in = k0 + srow < a.N, brow_in = j0 + srow < d;
-    const float* xa = a.X + (arow_in ? k0 + srow : 0) * d;
-    const float* mb = a.M + (brow_in ? j0 + srow : 0) * d;
-    f32x4 ra[4], rb[4];
-    int64_t tbase = 0;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63;
+    const int wm = wv / WN, wn = wv % WN;
+    const int op = wv >= TH / 128;                       // 0: X, 1: M
+    const int t = tid & (TH / 2 - 1);
+    const int kq = 4 * (t & 3), row0 = t >> 2;           // rows row0 + u GT / 4
+    const int64_t rbase = op ? j0 : k0, rows = op ? d : a.N;
+    const float* src = op ? a.M : a.X;
+    const float* p[4];
+    bool in[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int64_t row = rbase + row0 + u * (GT / 4);
+        in[u] = row < rows;
+        p[u] = src + (in[u] ? row : 0) * d;
+    }
+    f32x4 r[4];
     auto load = [&](int64_t t0) {
-        tbase = t0;
+        if (t0 + SPK <= d) {   // uniform: the chunk lies inside the rows
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int64_t t = t0 + sq + 4 * v;
-            if (VEC) {
-                const int64_t tc = t < d ? t : 0;   // d % 4 == 0: a whole chunk is in or out
-                ra[v] = *reinterpret_cast<const f32x4*>(xa + tc);
-                rb[v] = *reinterpret_cast<const f32x4*>(mb + tc);
-            } else {
+            for (int u = 0; u < 4; ++u) r[u] = *reinterpret_cast<const f32x4u*>(p[u] + t0 + kq);
+        } else {
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int64_t tc = t + u < d ? t + u : 0;
-                    ra[v][u] = xa[tc];
-                    rb[v][u] = mb[tc];
-                }
-            }
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) r[u][v] = t0 + kq + v < d ? p[u][t0 + kq + v] : 0.0f;
         }
     };
     auto store = [&](int sb) {
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const bool tin = tbase + sq + 4 * v + u < d;
-                ra[v][u] = (tin && arow_in) ? ra[v][u] : 0.0f;
-                rb[v][u] = (tin && brow_in) ? rb[v][u] : 0.0f;
-            }
-            *reinterpret_cast<f32x4*>(&As[sb][srow][sq + 4 * v]) = ra[v];
-            *reinterpret_cast<f32x4*>(&Bs[sb][srow][sq + 4 * v]) = rb[v];
-        }
+        for (int u = 0; u < 4; ++u)
+            split_store4(in[u] ? r[u] : f32x4{0.0f, 0.0f, 0.0f, 0.0f},
+                         &S[sb][(op * GT + row0 + u * (GT / 4)) * SPROW + kq], PLANE);
     };
-    f32x16 acc[2][2];
+    f32x16 acc[WX][WY];
 #pragma unroll
-    for (int x = 0; x < 2; ++x)
+    for (int x = 0; x < WX; ++x)
 #pragma unroll
-        for (int y = 0; y < 2; ++y) acc[x][y] = f32x16{0};
-    const int nch = (int)((d + GK - 1) / GK);
+        for (int y = 0; y < WY; ++y) acc[x][y] = f32x16{0};
+    const int nch = (int)((d + SPK - 1) / SPK);
     load(0);
     store(0);
     __syncthreads();
     for (int c = 0; c < nch; ++c) {
         const int sb = c & 1;
         const bool more = c + 1 < nch;
-        if (more) load((int64_t)(c + 1) * GK);
-        f32x4 fa[2][4], fb[2][4];
-#pragma unroll
-        for (int x = 0; x < 2; ++x)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                fa[x][v] = *reinterpret_cast<const f32x4*>(&As[sb][(2 * wm + x) * TS + lr][lk * 16 + v * 4]);
-                fb[x][v] = *reinterpret_cast<const f32x4*>(&Bs[sb][(2 * wn + x) * TS + lr][lk * 16 + v * 4]);
-            }
-#pragma unroll
-        for (int st = 0; st < 16; ++st)
-#pragma unroll
-            for (int x = 0; x < 2; ++x)
-#pragma unroll
-                for (int y = 0; y < 2; ++y)
-                    acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[x][st >> 2][st & 3],
-                                                                    fb[y][st >> 2][st & 3], acc[x][y],
-                                                                    0, 0, 0);
+        if (more) load((int64_t)(c + 1) * SPK);
+        split_mma<WX, WY>(&S[sb][wm * WX * 32 * SPROW], &S[sb][(GT + wn * WY * 32) * SPROW], PLANE, l, acc);
         if (more) store(sb ^ 1);
         __syncthreads();
     }
-    // acc[x][y][r] = Y(row (2wm + x) * 32 + (r >> 2) * 8 + lk * 4 + (r & 3),
-    //                  column (2wn + y) * 32 + lr); row sums of Y (.) X over the
-    // wave's 64 columns, then over the lanes of a row, then over the two waves
-    // that share the rows (wn = 0, 1)
+    // acc[x][y][q] = Y(row (WX wm + x) * 32 + (q >> 2) * 8 + (l >> 5) * 4 + (q & 3),
+    //                  column (WY wn + y) * 32 + (l & 31)); row sums of Y (.) X over
+    // the wave's columns, then over the lanes of a row, then over the waves that
+    // share the rows
+    const int lr = l & 31;
 #pragma unroll
-    for (int x = 0; x < 2; ++x)
+    for (int x = 0; x < WX; ++x)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int row = (2 * wm + x) * TS + (r >> 2) * 8 + lk * 4 + (r & 3);
+        for (int q = 0; q < 16; ++q) {
+            const int row = (WX * wm + x) * TS + (q >> 2) * 8 + (l >> 5) * 4 + (q & 3);
             const int64_t k = k0 + row;
             float v = 0.0f;
 #pragma unroll
-            for (int y = 0; y < 2; ++y) {
-                const int64_t j = j0 + (2 * wn + y) * TS + lr;
+            for (int y = 0; y < WY; ++y) {
+                const int64_t j = j0 + (WY * wn + y) * TS + lr;
                 const float xv = (k < a.N && j < d) ? a.X[k * d + j] : 0.0f;
-                v = fmaf(acc[x][y][r], xv, v);
+                v = fmaf(acc[x][y][q], xv, v);
             }
 #pragma unroll
             for (int off = 16; off >= 1; off >>= 1) v += __shfl_xor(v, off, 32);
             if (lr == 0) red[wn][row] = v;
         }
     __syncthreads();
-    if (tid < GB && k0 + tid < a.N) a.part[(int64_t)J * a.N + k0 + tid] = red[0][tid] + red[1][tid];
+    if (tid < GT && k0 + tid < a.N) {
+        float v = red[0][tid];
+#pragma unroll
+        for (int i = 1; i < WN; ++i) v += red[i][tid];
+        a.part[(int64_t)J * a.N + k0 + tid] = v;
+    }
 }
 
 __global__ __launch_bounds__(256) void k_quadform_reduce(const float* __restrict__ part, int nJ,
@@ -507,6 +503,13 @@ __global__ __launch_bounds__(256) void k_hadamard(const float* A, const float* B
     if (e < n) C[e] = A[e] * B[e];
 }
 
+static int device_cus() {
+    int dev = 0, ncu = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return 0;
+    if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
+    return ncu;
+}
+
 static size_t quadform_part_bytes(int64_t N, int64_t d) {
     return (size_t)((d + GB - 1) / GB) * (size_t)std::max<int64_t>(N, 1) * sizeof(float);
 }
@@ -514,26 +517,21 @@ static size_t quadform_part_bytes(int64_t N, int64_t d) {
 static hipError_t run_quadform(hipStream_t st, const float* X, int64_t N, int64_t d, const float* M,
                                float* w, float* part) {
     if (N == 0) return hipSuccess;
-    const int nJ = (int)std::max<int64_t>(1, (d + GB - 1) / GB);
+    // wide blocks where they fill the chip and do not pad a narrow d
+    const bool wide = d > GB && ((N + GBW - 1) / GBW) * ((d + GBW - 1) / GBW) >= device_cus();
+    const int64_t gt = wide ? GBW : GB;
+    const int nJ = (int)std::max<int64_t>(1, (d + gt - 1) / gt);
     QuadArgs a{X, N, d, M, nJ, part};
-    const bool vec = d % 4 == 0 && ((uintptr_t)X & 15) == 0 && ((uintptr_t)M & 15) == 0;
-    const dim3 grid((unsigned)(((N + GB - 1) / GB) * nJ));
-    if (vec)
-        hipLaunchKernelGGL(k_quadform<true>, grid, dim3(256), 0, st, a);
+    const dim3 grid((unsigned)(((N + gt - 1) / gt) * nJ));
+    if (wide)
+        hipLaunchKernelGGL((k_quadform<GBW, 4, 2>), grid, dim3(2 * GBW), 0, st, a);
     else
-        hipLaunchKernelGGL(k_quadform<false>, grid, dim3(256), 0, st, a);
+        hipLaunchKernelGGL((k_quadform<GB, 2, 2>), grid, dim3(2 * GB), 0, st, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_quadform_reduce, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, st, part,
                        nJ, N, w);
     return hipGetLastError();
-}
-
-static int device_cus() {
-    int dev = 0, ncu = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return 0;
-    if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-    return ncu;
 }
 
 }  // namespace bk

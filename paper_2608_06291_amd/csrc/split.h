@@ -1,0 +1,107 @@
+// fp32 products on the bf16 matrix cores, at fp32 precision.
+//
+// Every fp32 operand x is split without loss into three bf16 numbers,
+//     x = h + m + l :  h = x truncated to 8 bits, m = x - h rounded to 8 bits,
+//     l = the rest (at most 8 bits, so exact),
+// and a product a b is the sum of the six partial products
+//     l_a h_b + h_a l_b + m_a m_b + m_a h_b + h_a m_b + h_a h_b ,
+// each exact in fp32 (8 x 8 bits) and added into the fp32 accumulator of
+// v_mfma_f32_32x32x16_bf16, small ones first.  What is left out, m l + l m + l l,
+// is below 2^-22 of |a b| (2^-26 on average, of either sign: m is rounded to
+// nearest), under the half ulp that any fp32 summation loses at every step.
+// Sixteen k's share one rounding per partial product, against two k's per
+// rounding of v_mfma_f32_32x32x2f32.
+//
+// Why: the dense bf16 rate is 16 times the fp32 MFMA rate, six products leave
+// a factor 2.7 for the matrix cores (large products here reach 154 TFLOP/s in
+// fp32 and 1313 in bf16, so 219 for six products).  The split costs 5.5 VALU
+// operations per operand entry, which wide blocks amortise and which overlap
+// the MFMAs of the other wave on the SIMD.
+#pragma once
+#include "common.h"
+
+namespace bk {
+
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+
+constexpr int SPK = 16;      // k's per chunk: one MFMA step
+constexpr int SPROW = 24;    // bf16 slots per staged row: 16 k's in 48 bytes, so that the
+                             // 16-byte reads of 8 consecutive rows meet 8 different
+                             // 16-byte columns of the banks
+
+// bf16 pairs packed low, high
+struct SplitPair {
+    uint32_t h, m, l;
+};
+__device__ inline SplitPair split_pair(float a, float b) {
+    const uint32_t ua = __float_as_uint(a), ub = __float_as_uint(b);
+    SplitPair s;
+    s.h = __builtin_amdgcn_perm(ub, ua, 0x07060302u);   // the two high halves
+    const float ra = a - __uint_as_float(ua & 0xffff0000u);
+    const float rb = b - __uint_as_float(ub & 0xffff0000u);
+    s.m = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{ra, rb}, bf16x2));
+    const float ta = ra - __uint_as_float(s.m << 16);
+    const float tb = rb - __uint_as_float(s.m & 0xffff0000u);
+    s.l = __builtin_amdgcn_perm(__float_as_uint(tb), __float_as_uint(ta), 0x07060302u);
+    return s;
+}
+
+// Splits four consecutive k's of one row and writes the three planes
+// (`plane` bf16 slots apart) at dst.  A non-finite entry has m = l = NaN, so
+// every product with it is NaN (in plain fp32 it is infinite or NaN); products
+// without it are not touched.
+__device__ inline void split_store4(f32x4 v, uint16_t* dst, int plane) {
+    const SplitPair p = split_pair(v[0], v[1]), q = split_pair(v[2], v[3]);
+    *reinterpret_cast<u32x2*>(dst) = u32x2{p.h, q.h};
+    *reinterpret_cast<u32x2*>(dst + plane) = u32x2{p.m, q.m};
+    *reinterpret_cast<u32x2*>(dst + 2 * plane) = u32x2{p.l, q.l};
+}
+
+// One chunk of a wave's WX x WY blocks of 32 x 32: acc[x][y] += A_x B_y^T over
+// the 16 staged k's.  a, b: plane 0 of the wave's first A and B row; lane l
+// reads k's 8 (l >> 5) .. + 7 of row l & 31 of each block.
+template <int WX, int WY>
+__device__ inline void split_mma(const uint16_t* a, const uint16_t* b, int plane, int l,
+                                 f32x16 (&acc)[WX][WY]) {
+    const int off = (l & 31) * SPROW + (l >> 5) * 8;
+    bf16x8 fb[WY][3];
+#pragma unroll
+    for (int y = 0; y < WY; ++y)
+#pragma unroll
+        for (int s = 0; s < 3; ++s)
+            fb[y][s] = *reinterpret_cast<const bf16x8*>(b + y * 32 * SPROW + s * plane + off);
+    // (plane of A, plane of B), small products first.  The chunk's sum starts
+    // from zero and is added to the running sum once: one rounding at the
+    // running sum's size per 16 k's.  A block is added while the MFMAs of the
+    // next one run.
+    constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};
+    f32x16 t[2];
+#pragma unroll
+    for (int x = 0; x < WX; ++x) {
+        bf16x8 fa[3];
+#pragma unroll
+        for (int s = 0; s < 3; ++s)
+            fa[s] = *reinterpret_cast<const bf16x8*>(a + x * 32 * SPROW + s * plane + off);
+#pragma unroll
+        for (int y = 0; y < WY; ++y) {
+            const int i = x * WY + y;
+            t[i & 1] = f32x16{0};
+#pragma unroll
+            for (int p = 0; p < 6; ++p)
+                t[i & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[PA[p]], fb[y][PB[p]], t[i & 1], 0, 0, 0);
+            if (i > 0) {
+                f32x16& c = acc[(i - 1) / WY][(i - 1) % WY];
+                c += t[(i - 1) & 1];
+                asm volatile("" : "+v"(c));   // add here: t must not stay live
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    acc[WX - 1][WY - 1] += t[(WX * WY - 1) & 1];
+    asm volatile("" : "+v"(acc[WX - 1][WY - 1]));
+}
+
+}  // namespace bk

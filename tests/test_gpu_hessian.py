@@ -73,6 +73,36 @@ def test_gram_parity(oracle_mod, N, d, weighted, masked):
         assert np.array_equal(C, C.T), "C must be exactly symmetric"
 
 
+@pytest.mark.parametrize("N,d", [(15, 127), (16, 128), (17, 129), (20, 255), (35, 256), (5000, 257),
+                                 (9000, 515), (3, 2)])
+def test_gram_and_quadform_block_edges(oracle_mod, N, d):
+    """Chunk (16 samples), block (128 and 256) and matrix-end remainders, rows at
+    every 4-byte alignment, both block sizes; and an infinite entry makes its own
+    row and column non-finite and leaves the others as they are."""
+    import torch
+    import paper_2608_06291_amd as pk
+    h = oracle_mod.hessian
+    log(f"case edges N={N} d={d}")
+    r = np.random.Generator(np.random.PCG64(np.random.SeedSequence([4010, N, d])))
+    X = (workloads.ar1_samples(N, d, 0.5, r) * np.exp(r.uniform(-8, 8, (1, d)))).astype(np.float32)
+    w = r.standard_normal(N).astype(np.float32)
+    flat = torch.empty(N * d + 1, device="cuda:0")   # X one float past a 16-byte boundary
+    Xd = flat[1:].view(N, d)
+    Xd.copy_(_dev(X))
+    C = pk.gram(Xd, _dev(w), 0.5).cpu().numpy()
+    _check(C, 0.5 * N * h.expect_outer(X, w), _abssum(X, w, 0.5), N, d, f"edges{N}x{d}")
+    Z = r.standard_normal((d, 4))
+    M = (Z @ Z.T).astype(np.float32)
+    q = pk.quadform_weights(Xd, _dev(M)).cpu().numpy().astype(np.float64)
+    X64, M64 = X.astype(np.float64), M.astype(np.float64)
+    bound = (2 * d + 8) * U32 * np.sum((np.abs(X64) @ np.abs(M64)) * np.abs(X64), axis=1)
+    assert np.all(np.abs(q - np.sum((X64 @ M64) * X64, axis=1)) <= bound + 1e-30)
+    Xd[N - 1, d - 1] = float("inf")
+    Ci = pk.gram(Xd, _dev(w), 0.5).cpu().numpy()
+    assert np.array_equal(Ci[:d - 1, :d - 1], C[:d - 1, :d - 1])
+    assert not np.isfinite(Ci[d - 1]).any()
+
+
 def test_gram_in_place_mask_empty_and_deterministic(oracle_mod):
     import torch
     import paper_2608_06291_amd as pk
