@@ -139,7 +139,7 @@ bakron_status bakron_factor(const float *A, int64_t n, const float *B, int64_t m
  * never with BAKRON_DEFER=0.  When the cost model picks the two-stream plan
  * (BAKRON_DEFER unset), the first solve of that shape on the handle runs
  * both plans twice each, times them with events on `stream` (one host
- * synchronisation), keeps the faster for the handle and returns the outputs
+ * synchronisation), keeps two streams for the handle if they are more than 3% faster, and returns the outputs
  * of its last run (not while per-launch profiling is enabled, which keeps
  * the model's choice).  On the legacy default stream, which
  * synchronises implicitly with such streams, and while `stream` is being

@@ -596,8 +596,9 @@ static bool masked_streams(int device, int ncu, int R, hipStream_t* main, hipStr
 // sequential chain); a node push a fixed launch cost plus its MFMA flops at
 // a per-CU rate on the CUs of its stream, a side push a larger fixed cost.
 // The constants are fitted to MI355X solve times of twelve layer shapes
-// (3072^2 to 14336 x 4096) under both plans; only the comparison of the two
-// plans for one shape uses them.
+// (3072^2 to 14336 x 4096) under both plans, with earlier kernels (a tile
+// anti-diagonal of a segment now takes 11 us); only the comparison of the two
+// plans for one shape uses them, and a choice of two streams is timed.
 static double plan_model_seconds(const bk::Plan& p, int cus_main, int cus_side) {
     const double t_diag = 13.4e-6, t_seg = 3e-6, t_node = 6e-6, t_side = 30e-6, t_wait = 40e-6;
     const double rate_cu = 0.45e12;
@@ -965,7 +966,13 @@ static bakron_status solve_impl(const float* W, int64_t m, int64_t n, const bakr
                 if (e == hipSuccess && rep == 1) e = hipEventElapsedTime(&t[plan], f->tev[0], f->tev[1]);
             }
         if (e != hipSuccess) return hip_fail(&f->err, e, "bakron_solve: timing the plans");
-        if (t[0] <= t[1]) {   // one stream from now on for this handle and shape
+        // One stream from now on for this handle and shape, unless two are more
+        // than 3% faster: two-stream solves of all handles share one pair of
+        // streams and run one after the other, while one-stream solves on
+        // different streams overlap (4096 x 4096 alone: 3.94 ms with one stream,
+        // 3.93 with two; three handles on three streams in turn: 2.3 ms per solve
+        // with one, 3.9 with two).
+        if (t[0] <= 1.03f * t[1]) {
             f->plan[1] = bk::Plan{};
             pi = 0;
         }

@@ -32,6 +32,7 @@
 // apart than KNEAR, so each (source, target) tile pair is applied exactly
 // once.
 #include <algorithm>
+#include <type_traits>
 
 #include "common.h"
 
@@ -56,14 +57,14 @@ struct SegArgs {
     float* V;
     float* pre;       // may be null
     int knear;        // pull distances 1..knear (<= KNEAR_MAX)
-    int* flags;       // per tile: 1 once F of the tile is published
+    int* flags;       // per tile: 1 once rows 0 .. 15 of F are published, 2 once all are
     int* counter;     // strip ticket counter of this launch, 0 at entry
     int* status;      // set to 1 if a wait gave up (never in a correct run); sticky
     int spin_limit;   // polls before a wait gives up
 };
 
-// Bounded wait for a tile's ready flag, executed by a whole wave (uniform
-// address).  A strip only ever waits for strips with smaller tickets, and
+// Bounded wait for a tile's ready flag to reach `level`, executed by a whole
+// wave (uniform address).  A strip only ever waits for strips with smaller tickets, and
 // tickets are handed out only to running workgroups, so the flag is set by a
 // running workgroup; the bound only turns a logic error into a reported
 // failure instead of a hang.  Once a wait has given up, the status word stays
@@ -71,9 +72,9 @@ struct SegArgs {
 // once, so a failed solve, and every solve after it, ends quickly with its
 // output marked invalid.  The data behind the flag is read with
 // device-coherent (sc1) loads, so no cache invalidation is needed here.
-__device__ inline void wait_ready(const int* flag, int* status, int spin_limit) {
+__device__ inline void wait_ready(const int* flag, int level, int* status, int spin_limit) {
     int it = 0;
-    while (__hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0) {
+    while (__hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < level) {
         __builtin_amdgcn_s_sleep(1);
         if (++it >= spin_limit ||
             __hip_atomic_load(status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
@@ -95,8 +96,8 @@ constexpr int CPOL_SC1 = 16;   // device-coherent load / store
 // a tile are two 32 x 32 products per source distance k:
 //   row kind    (into X): C[q][p] += sum_j L^A[J, J-k][q][j] F[I, J-k][p][j]
 //   column kind (into Y): C[p][q] += sum_i L^B[I, I-k][p][i] E[I-k, J][i][q]
-// Waves 0-3 own one 16 x 16 block of the row-kind C each, waves 4-7 one block
-// of the column-kind C, so no partial sums have to be combined.  Every
+// Every pull wave owns one 16 x 16 block of one of the two, so no partial sums
+// have to be combined.  Every
 // operand is read as contiguous 16-byte chunks of a row: lane (i, s) of a
 // 16 x 16 x 4 step supplies A[i][k] and B[k][i] with k = 8s + 4c + t at step
 // (c, t), i.e. chunks 2s and 2s + 1 of row i of both operand tiles.
@@ -124,79 +125,138 @@ __device__ inline void stage_rows(const float* src, float* dst, int rb, int l) {
 }
 
 constexpr int RING = KNEAR_MAX;   // E tiles of the strip kept in LDS
-constexpr int RSTR = TS + 4;      // ring row stride: 16-byte rows, conflict-free b128 reads
-constexpr int PULL_T0 = 2;        // first loop turn whose idle waves may consume staged operands
+constexpr int RSTR = TS + 4;      // LDS row stride: 16-byte rows, conflict-free b128 reads
 
 // Persistent solve of the tiles on anti-diagonals [K, L) by tile-column
-// strips.  Each workgroup (512 threads, one per CU) repeatedly takes a strip
-// ticket and solves the strip's tiles in [K, L) top to bottom; strip J waits
-// only for strips J-1 .. J-2, which hold smaller tickets.  Inside a strip the
-// column dependencies are local: the last RING errors E of the strip stay in
-// LDS, and so do L^A[J, J-k] for k = 1..knear.  Per tile I:
-//  1. pull.  The sources at distance k >= 2 of tile I are complete while
-//     tile I-1 is being rounded (tile (I, J-2) finished before tile (I-1, J)
-//     started, and every tile waits for its left neighbour, so one flag
-//     stands for the whole row to its left).  Their operands are staged in
-//     LDS at the start of tile I-1's rounding loop and the waves multiply them
-//     in the loop turns in which they are idle; what remains (the first tile
-//     of a strip, or a left strip that was late) is done here, followed by
-//     distance 1: the row source (I, J-1) after its ready flag (device-
-//     coherent loads) and the column source E(I-1) from the ring.  The 16 x 16
-//     blocks meet in LDS;
-//  2. in-tile rounding of the 63 element anti-diagonals (below);
-//  3. publish F -> Y: the tile is gathered in LDS and written as whole
-//     128-byte rows with device-coherent (sc1) 16-byte stores, which the
-//     memory system acknowledges much sooner than scattered 4-byte ones; wait
-//     for them, set the tile's flag.  E goes to the ring and to X (read by the
-//     node launches after this one);
-//  4. codes, V and pre, gathered in LDS and written as row segments.
+// strips.  Each workgroup (one per CU) repeatedly takes a strip ticket and
+// solves the strip's tiles in [K, L) top to bottom; strip J waits only for
+// strips J-1 .. J-2, which hold smaller tickets.  Inside a strip the column
+// dependencies are local: the last RING errors E of the strip stay in LDS, and
+// so do L^A[J, J-k] for k = 1..knear.
 //
-// In-tile rounding: each thread owns two entries of one row p: slot 0 at
-// column q0 and slot 1 at column q1 = q0 + 1 (mod 32), so p + q1 = p + q0 + 1.
-// Half-wave h of wave w owns the rows' entries whose anti-diagonal index is
-// {4w + 2h, 4w + 2h + 1} mod 32: two consecutive element anti-diagonals d
-// (slot 0) and d + 1 (slot 1) are handled by the same half-wave, one barrier
-// per pair.  Within a pair, the only feedback from diagonal d into d + 1 is
-// the error of the entry just above (row p - 1, same column: one lane down,
-// DPP wave_shr:1) through L^B[p][p-1], and the F of the entry just to the
-// left (the thread's own slot 0) through L^A[q1][q0] (Eq. (1) restricted to
-// the two diagonals).  After the barrier every thread adds the column pushes
-// L^B[p][i] * E[i][q] and row pushes F[p][j] * L^A[q][j] of both diagonals to
-// both of its entries.  Coefficients are register-resident, each factor row
-// rotated so that step d reads register (d mod 32).
-// GQ: scales per column group and/or per column (else one scale per row, the
-// same for both entries of a thread).  ASYM: alphabet {qlo..qhi} (else the
-// symmetric {-qhi..qhi}, clamped with one scalar operand).
-template <bool GQ, bool ASYM>
-__global__ __launch_bounds__(512) void k_seg(SegArgs a) {
-    __shared__ float LBt[TS][TS];            // unpadded: the rotated reads below are conflict-free
-    __shared__ float LAt[TS][TS];
-    __shared__ float Ecs[2][2][2][2 * TS];   // [turn parity][round][diagonal of the pair][column (+ dummies)]
-    __shared__ float2 Frs[2][2][2 * TS];     // [turn parity][round][row (+ dummies)] = (F on d, F on d + 1)
-    __shared__ float HR[TS][TS + 1];         // pulled row-kind sum, [q][p]
-    __shared__ float GC[TS][TS + 1];         // pulled column-kind sum, [p][q]
-    __shared__ __attribute__((aligned(16))) float Ering[RING][TS][RSTR];   // E^T[q][i] per tile
-    __shared__ __attribute__((aligned(16))) float LAs[KNEAR_MAX][TILE_ELEMS];      // L^A[J, J-k-1]
-    __shared__ __attribute__((aligned(16))) float LBn[KNEAR_MAX][TILE_ELEMS];      // L^B[I', I'-k-1]
-    __shared__ __attribute__((aligned(16))) float Yn[KNEAR_MAX - 1][TILE_ELEMS];   // F[I', J-k-2]
-    __shared__ __attribute__((aligned(16))) float Fst[TS][RSTR];   // F of the tile, row-major
-    __shared__ float So[GQ ? TS : 1][TS + 1];   // scales of the tile's entries (per row without GQ)
-    __shared__ int tk, ynext;
+// What bounds it: the chain of dependent element anti-diagonals (63 per tile,
+// one tile after the other), so everything that is not on that chain is kept
+// off the one wave that walks it.  Roles of the 12 waves:
+//   solver (wave 0): the in-tile rounding, in registers.  Lanes 0..31 hold the
+//     column sums G of rows 0..31, lanes 32..63 the row sums H; at step t lane
+//     p is at entry (p, t - p).  A step adds the errors of the last SG to
+//     2 SG - 1 anti-diagonals (below), exchanges G and H between the halves
+//     (v_permlane32_swap), rounds, and writes E, F and x to LDS.
+//   pull waves (8): one 16 x 16 block of G or H each, on fp32 MFMA
+//     (v_mfma_f32_16x16x4f32).  Every SG anti-diagonals (a group) a barrier
+//     hands them the errors of the group just finished; during the next group
+//     they add its pushes into the whole tile and pass the entries of the
+//     group after that to the solver through LDS.  So an entry's sources
+//     within its own and the previous group are the solver's, all older ones
+//     theirs.  In between they multiply the near-field sources of the next tile.
+//   service waves (3): publish F of the finished tile, write codes, V and pre,
+//     copy E to X, stage the next tile's operands in LDS.
+// A wave alone issues about one operation per 6.5 cycles (measured), so the
+// solver's time is its number of operations: per step 2 per source (a lane
+// shift of the column half's history and a multiply-add that serves both
+// halves) and about 25 others, 265 cycles at SG = 8.  A larger SG costs more
+// sources, a smaller one more barriers and less time for the pull waves: SG = 7
+// made the segments of the 4096 x 4096 layer 8% longer, SG = 4 37%.
+// Measured against the kernel before it, in which all eight waves took turns
+// at the rounding and met at a barrier per 4 anti-diagonals: 12.7 -> 10.7 us
+// per tile anti-diagonal (4096 x 4096), 13.3 -> 11.2 (28672 x 8192), the 64 x 64
+// layer 34.6 -> 29.9 us in all.  Of a tile's 23000 cycles 2600 go to the sums
+// of the block at its origin before the solver can start (flag and F of the
+// left tile), 17100 to its steps, the rest to waiting for the pull waves of the
+// blocks with the most pushes.
+//
+// Per tile I:
+//  1. pull.  The sources at distance k >= 2 are complete while tile I-1 is
+//     being rounded, up to the last of them; their operands are staged and
+//     multiplied beside that (stage_index, use_group) once the left strips'
+//     flags are up.  What was late is done here.  Then distance 1: F[I, J-1]
+//     after its ready flag (device-coherent loads) and E(I-1) from the ring,
+//     for the block at the origin before the solver starts, for the others
+//     beside its first groups.
+//  2. the 63 element anti-diagonals, in NGRP groups with a barrier each.
+//  3. F -> Y with device-coherent (sc1) 16-byte stores of whole rows, rows 0 .. 15
+//     as soon as they are complete (flag 1), the rest after the last group
+//     (flag 2); E -> X (read by the node launches after this one); codes, V and
+//     pre.  The service waves do this beside the next tile's start.
+// GQ: scales per column group and/or per column (else one scale per row).
+// ASYM: alphabet {qlo..qhi} (else the symmetric {-qhi..qhi}).
+constexpr int SEG_THREADS = 768;
+constexpr int SG = 8;                                  // anti-diagonals per group
+constexpr int NGRP = (2 * TS - 1 + SG - 1) / SG;       // groups per tile
+constexpr int NSRC = 2 * SG - 1;                       // the solver's own source distances
+constexpr int NV = (NSRC + 3) / 4;                     // in 16-byte pieces
+constexpr int TROW = 4 * (NV | 1);                     // row stride of the coefficient tables:
+                                                       // an odd number of 16-byte pieces
+// The next tile's operands are staged in the order F[8], L^B[8], F[7], L^B[7],
+// .., F[2], L^B[2], L^B[1] (by source distance), one tile per service wave and
+// group; a group later they have landed, and in the group after that the pull
+// waves may use them (use_group), one source per group.
+__device__ constexpr int stage_index(int k, bool lb) { return k == 1 ? 14 : 2 * (KNEAR_MAX - k) + (lb ? 1 : 0); }
+__device__ constexpr int use_group(int k, bool lb) { return 2 + stage_index(k, lb) / 3; }
+constexpr int POLL_G = 2;                              // group in which the flag of (I + 1, J - 2) is polled
+constexpr int PUB_G = (TS + TS / 2 - 1 + SG - 1) / SG; // rows 0 .. 15 are complete once this group begins
+static_assert(2 * SG <= TS / 2 && PUB_G + 1 < NGRP && use_group(2, true) < NGRP && POLL_G % 2 == 0 &&
+              POLL_G < stage_index(2, false) / 3, "group schedule");
+// LDS layout (floats)
+constexpr int S_RING = 0;                              // [RING][TS][RSTR]  E^T[q][i] per tile
+constexpr int S_LA = S_RING + RING * TS * RSTR;        // [KNEAR_MAX] tiles L^A[J, J-k-1]
+constexpr int S_LB = S_LA + KNEAR_MAX * TILE_ELEMS;    // [KNEAR_MAX] tiles L^B[I', I'-k-1]
+constexpr int S_Y = S_LB + KNEAR_MAX * TILE_ELEMS;     // [KNEAR_MAX - 1] tiles F[I', J-k-2]
+constexpr int S_F = S_Y + (KNEAR_MAX - 1) * TILE_ELEMS;   // [TS][RSTR] F of the tile
+constexpr int S_X = S_F + TS * RSTR;                   // [TS][RSTR] x of the tile
+constexpr int S_BASE = S_X + TS * RSTR;                // [2][SG][64] sums handed to the solver
+constexpr int S_TA = S_BASE + 2 * SG * 64;             // [TS][TROW] L^A[q][q-k]
+constexpr int S_TB = S_TA + TS * TROW;                 // [TS][TROW] L^B[p][p-k]
+constexpr int S_END = S_TB + TS * TROW;
+constexpr int S_SC = S_END;                            // GQ: [TS][TS + 1] scales, then reciprocals
+constexpr int S_END_GQ = S_SC + 2 * TS * (TS + 1);
+// the solver's lanes outside the tile read up to TS - 1 rows before and 2 TS - 1
+// rows after the first row of S_TA; their results are masked
+static_assert((TS - 1) * TROW <= S_TA && 2 * TS * TROW <= S_END - S_TA, "coefficient reads stay in LDS");
+static_assert(S_END_GQ * 4 + 64 <= 160 * 1024, "LDS");
 
-    const int tid = threadIdx.x;
-    const int w = tid >> 6, l = tid & 63;
-    const int hf = l >> 5;
-    const int p = l & 31;
-    const int c0 = 4 * w + 2 * hf;
-    const int q0 = (c0 - p) & 31;
-    const int q1 = (q0 + 1) & 31;
+enum SegRole { SOLVER, PULL, SERVICE };
+typedef __attribute__((address_space(3))) char lds_char;
+typedef __attribute__((address_space(3))) f32x4 lds_f32x4;
+
+// Workgroup barrier that orders LDS (also the writes the compiler does not see
+// inside the solver's asm); global loads and stores stay in flight.
+__device__ inline void seg_sync() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0)
+    __syncthreads();
+}
+
+// The whole kernel for one role (the same statements and barriers for all
+// three; what a role does not do is removed at compile time, so that the
+// registers of the roles are not live at once).  W: the wave's number within
+// its role.
+template <bool GQ, bool ASYM, int ROLE>
+__device__ __forceinline__ void seg_role(const SegArgs& a, float* sm, int& tk, volatile int* yready, int w, int W) {
+    const int tid = threadIdx.x, l = tid & 63;
+    const int hf = l >> 5, p = l & 31;
     const float qhi = a.q.qhi, qlo = ASYM ? a.q.qlo : -qhi;
     const int knear = a.knear;
-    const bool roww = w < 4;   // wave-uniform: row-kind or column-kind pull blocks
+    constexpr bool solver = ROLE == SOLVER, pull = ROLE == PULL;
+    const int sv = ROLE == SERVICE ? W : -1;
+    const int mb = W;                // pull block 0..7
+    const bool roww = mb < 4;        // row-kind (C[q][p]) or column-kind (C[p][q]) block
+    const int i16 = l & 15, ks = l >> 4;
+    const int ra0 = 16 * ((mb & 3) >> 1), rb0 = 16 * (mb & 1), rb = rb0 + i16, ra = ra0 + i16;
+    // the block at the tile's origin has all entries of the groups 0 and 1: its
+    // two waves finish their sums before the solver starts; the others do it in
+    // group 0, and the row-kind waves of the lower half, whose sources the left
+    // strip publishes last, in group 1
+    const bool lead = ra0 + rb0 == 0;
+    const int base_g = lead ? -1 : roww && rb0 ? 1 : 0;
+    // output items of the service waves 1 and 2: rows r0, r0 + 16, columns cb .. cb + 3
+    const int ot = 64 * (sv - 1) + l, r0 = (ot >> 3) & 15, cb = 4 * (ot & 7);
+
+    if (solver) __builtin_amdgcn_s_setprio(3);
 
     for (;;) {
         if (tid == 0) tk = atomicAdd(a.counter, 1);
-        __syncthreads();
+        seg_sync();
         const int sidx = tk;
         if (sidx >= a.nstrips) break;   // uniform
         const int J = a.J_lo + sidx;
@@ -205,370 +265,444 @@ __global__ __launch_bounds__(512) void k_seg(SegArgs a) {
         const int kr = knear < J ? knear : J;   // row sources k = 1..kr of every tile of the strip
         const bool need_y = kr >= 2;
 
-        // strip set-up: L^A[J, J] and L^A[J, J-k], the ring with the errors of
-        // the tiles above that were solved by earlier launches, the first
-        // tile's inputs and its staged pull operands.  Every load is issued
-        // before any is waited for: one memory round trip per strip.
-        const int npre = a.b_ident ? 0 : (knear < I_first ? knear : I_first);
-        float2 rg[KNEAR_MAX];
+        // the column part of the scales of the thread's output columns
+        ColScale cs[4];
 #pragma unroll
-        for (int k = 0; k < KNEAR_MAX; ++k)
-            if (k < npre)   // uniform
-                rg[k] = *reinterpret_cast<const float2*>(a.X + ws_tile_offset(I_first - 1 - k, J, a.nt) +
-                                                          2 * tid);   // E^T, column-major E
-        const float lat0 = a.LA[packed_tile_offset(J, J) + tid];
-        const float lat1 = a.LA[packed_tile_offset(J, J) + tid + 512];
-        for (int g = w; g < 4 * kr; g += 8)
-            stage_rows<0>(a.LA + packed_tile_offset(J, J - 1 - (g >> 2)), LAs[g >> 2], g & 3, l);
+        for (int v = 0; v < 4; ++v)
+            cs[v] = GQ && sv >= 1 ? col_scale_of(a.q, (int64_t)J * TS + cb + v, a.n) : ColScale{0, 1.0f};
 
-        // inputs of the first tile; later tiles' inputs are prefetched during
-        // the previous tile's rounding loop
-        float pf_lb0, pf_lb1, pf_h0, pf_h1, pf_g0, pf_g1, pf_s0, pf_s1;
-        // the column part of the scales of the thread's two columns (fixed per strip)
-        const ColScale cs0 = GQ ? col_scale_of(a.q, (int64_t)J * TS + q0, a.n) : ColScale{0, 1.0f};
-        const ColScale cs1 = GQ ? col_scale_of(a.q, (int64_t)J * TS + q1, a.n) : cs0;
-        {
-            const int64_t tb = ws_tile_offset(I_first, J, a.nt);
-            const float* lbp = a.LB + packed_tile_offset(I_first, I_first);
-            pf_lb0 = a.b_ident ? 0.0f : lbp[tid];
-            pf_lb1 = a.b_ident ? 0.0f : lbp[tid + 512];
-            pf_h0 = a.X[tb + q0 * TS + p];
-            pf_h1 = a.X[tb + q1 * TS + p];
-            pf_g0 = a.Y[tb + p * TS + q0];
-            pf_g1 = a.Y[tb + p * TS + q1];
-            const int row = I_first * TS + p;
-            pf_s0 = row_scale_of<GQ>(a.q, row, cs0, a.m);
-            pf_s1 = GQ ? row_scale_of<GQ>(a.q, row, cs1, a.m) : 0.0f;
-        }
-        // the first tile's pull operands: L^B[I_first, I_first - k] and the
-        // left strips' F[I_first, J - k], k >= 2 (after the flag of
-        // (I_first, J - 2), which stands for the whole row to its left)
-        {
-            const int nlb = npre;
-            if (need_y) wait_ready(a.flags + I_first * a.nt + (J - 2), a.status, a.spin_limit);
-            const int lim = 4 * (nlb + (need_y ? kr - 1 : 0));
-            const int wu = __builtin_amdgcn_readfirstlane(w);
-            __atomic_signal_fence(__ATOMIC_SEQ_CST);   // the F loads stay after the flag test
+        // inputs of a tile, loaded while the tile before it is solved:
+        // pull waves their block of X or Y and, column kind, their rows of the
+        // diagonal tile of L^B; the solver its rows' scales; service waves
+        // the solver's L^B coefficients and the scales of their output entries
+        float pfx[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+        f32x4 pfl0 = {0.0f, 0.0f, 0.0f, 0.0f}, pfl1 = pfl0;
+        float pfs = 0.0f, pft[8], pfo[2][GQ ? 4 : 1];
+        auto prefetch = [&](int In) {
+            const int64_t tb = ws_tile_offset(In, J, a.nt);
+            const float* lbp = a.LB + packed_tile_offset(In, In);
+            if (pull) {
+                const float* src = (roww ? a.X : a.Y) + tb + (ra0 + 4 * ks) * TS + rb;
 #pragma unroll
-            for (int i = 0; i < (4 * (2 * KNEAR_MAX - 1) + 7) / 8; ++i) {
-                const int g = wu + 8 * i;
-                if (g < lim) {
-                    const int ti = g >> 2;
-                    if (ti < nlb)
-                        stage_rows<0>(a.LB + packed_tile_offset(I_first, I_first - 1 - ti), LBn[ti], g & 3, l);
-                    else
-                        stage_rows<CPOL_SC1>(a.Y + ws_tile_offset(I_first, J - 2 - (ti - nlb), a.nt),
-                                             Yn[ti - nlb], g & 3, l);
+                for (int r = 0; r < 4; ++r) pfx[r] = src[r * TS];
+                if (!roww && !a.b_ident) {
+                    pfl0 = *reinterpret_cast<const f32x4*>(lbp + ra * TS + 8 * ks);
+                    pfl1 = *reinterpret_cast<const f32x4*>(lbp + ra * TS + 8 * ks + 4);
+                }
+            } else if (solver) {
+                if (!GQ) pfs = row_scale_of<GQ>(a.q, (int64_t)In * TS + p, ColScale{0, 1.0f}, a.m);
+            } else {
+                if (sv == 1) {
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) {
+                        const int k = 8 * hf + j + 1;
+                        pft[j] = (k <= p && !a.b_ident) ? lbp[p * TS + p - k] : 0.0f;
+                    }
+                }
+                if (sv >= 1) {
+#pragma unroll
+                    for (int j = 0; j < 2; ++j)
+#pragma unroll
+                        for (int v = 0; v < (GQ ? 4 : 1); ++v)
+                            pfo[j][v] = row_scale_of<GQ>(a.q, (int64_t)In * TS + r0 + 16 * j, cs[v], a.m);
                 }
             }
-        }
-        LAt[tid >> 5][tid & 31] = lat0;
-        LAt[(tid + 512) >> 5][tid & 31] = lat1;
-#pragma unroll
-        for (int k = 0; k < KNEAR_MAX; ++k)
-            if (k < npre)
-                *reinterpret_cast<float2*>(&Ering[(I_first - 1 - k) % RING][(2 * tid) >> 5][(2 * tid) & 31]) = rg[k];
-        __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): this wave's direct loads landed
-        __syncthreads();
+        };
+        // issue the direct loads of one operand tile by the waves wi, wi + nw, ...
+        auto stage_lb = [&](int It, int k, int wi, int nw) {   // L^B[It, It-k]
+            for (int g = wi; g < 4; g += nw)   // uniform control flow
+                stage_rows<0>(a.LB + packed_tile_offset(It, It - k), sm + S_LB + (k - 1) * TILE_ELEMS, g, l);
+        };
+        auto stage_y = [&](int It, int k, int wi, int nw) {    // F[It, J-k], k >= 2
+            for (int g = wi; g < 4; g += nw)
+                stage_rows<CPOL_SC1>(a.Y + ws_tile_offset(It, J - k, a.nt), sm + S_Y + (k - 2) * TILE_ELEMS, g, l);
+        };
 
-        // pull state of the next tile (uniform): which operands are staged,
-        // and per wave the next source distance to multiply
-        bool lb_staged = true, y_staged = true;   // the first tile's, above
-        int nk = 2;
+        // strip set-up: L^A[J, J-k], the coefficients of L^A[J, J], the ring with
+        // the errors of the tiles above that were solved by earlier launches,
+        // the first tile's inputs and its staged pull operands.  Every load is
+        // issued before any is waited for: one memory round trip per strip.
+        const int npre = a.b_ident ? 0 : (knear < I_first ? knear : I_first);
+        const float* lad = a.LA + packed_tile_offset(J, J);
+        {
+            float2 rg[KNEAR_MAX];
+#pragma unroll
+            for (int k = 0; k < KNEAR_MAX; ++k)
+                if (k < npre && tid < 512)
+                    rg[k] = *reinterpret_cast<const float2*>(a.X + ws_tile_offset(I_first - 1 - k, J, a.nt) +
+                                                              2 * tid);   // E^T, column-major E
+            const int tq = tid / NSRC, tkk = tid - tq * NSRC + 1;
+            float lac = 0.0f;
+            static_assert(TS * NSRC <= SEG_THREADS, "one coefficient per thread");
+            if (tq < TS && tkk <= tq) lac = lad[tq * TS + tq - tkk];
+            for (int g = w; g < 4 * kr; g += SEG_THREADS / 64)
+                stage_rows<0>(a.LA + packed_tile_offset(J, J - 1 - (g >> 2)), sm + S_LA + (g >> 2) * TILE_ELEMS, g & 3, l);
+            prefetch(I_first);
+            for (int g = w; g < 4 * npre; g += SEG_THREADS / 64) stage_lb(I_first, 1 + (g >> 2), g & 3, 4);
+            if (need_y) {
+                wait_ready(a.flags + I_first * a.nt + (J - 2), 2, a.status, a.spin_limit);
+                for (int g = w; g < 4 * (kr - 1); g += SEG_THREADS / 64) stage_y(I_first, 2 + (g >> 2), g & 3, 4);
+            }
+            if (tq < TS) sm[S_TA + tq * TROW + tkk - 1] = lac;
+#pragma unroll
+            for (int k = 0; k < KNEAR_MAX; ++k)
+                if (k < npre && tid < 512)
+                    *reinterpret_cast<float2*>(&sm[S_RING + ((I_first - 1 - k) % RING) * (TS * RSTR) +
+                                                   ((2 * tid) >> 5) * RSTR + ((2 * tid) & 31)]) = rg[k];
+        }
+        f32x4 lf0 = {0.0f, 0.0f, 0.0f, 0.0f}, lf1 = lf0;   // rows ra of the diagonal tile (L^A, or the tile's L^B)
+        if (pull && roww) {
+            lf0 = *reinterpret_cast<const f32x4*>(lad + ra * TS + 8 * ks);
+            lf1 = *reinterpret_cast<const f32x4*>(lad + ra * TS + 8 * ks + 4);
+        }
+        __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): this wave's direct loads landed
+        seg_sync();
+
+        // F[., J-k] of the tile staged for k = 2 and for k >= 3 (uniform; the
+        // first tile's were staged above)
+        bool y2 = true, y3 = true;
+        // per wave: the next source distance to multiply, from the farthest down to 2
+        int nk = roww ? kr : npre;
         f32x4 pacc = {0.0f, 0.0f, 0.0f, 0.0f};
 
         for (int I = I_first; I <= I_last; ++I) {
-            // lane constants are recomputed per tile from an opaque copy of the
-            // thread index, so the compiler does not keep every derived LDS
-            // address of the unrolled loop below live across tiles
-            int tid = threadIdx.x;
-            asm volatile("" : "+v"(tid));
-            const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), l = tid & 63;   // w: wave-uniform
-            const int hf = l >> 5;
-            const int p = l & 31;
-            const int c0 = 4 * w + 2 * hf;
-            const int q0 = (c0 - p) & 31;
-            const int q1 = (q0 + 1) & 31;
-            const int i16 = l & 15, ks = l >> 4;
-            // pull block of this wave: A-operand rows ra0 + i16, B-operand rows rb
-            const int ra0 = roww ? 16 * (w >> 1) : 16 * ((w - 4) >> 1);
-            const int rb = (roww ? 16 * (w & 1) : 16 * ((w - 4) & 1)) + i16;
-            const int ra = ra0 + i16;
-            const int64_t tbase = ws_tile_offset(I, J, a.nt);
-            float* const Xg = a.X + tbase;   // X tile: column-major
-            float* const Yg = a.Y + tbase;   // Y tile: row-major
-            {
-                const int e0 = tid, e1 = tid + 512;   // LBt rows e >> 5, columns e & 31
-                LBt[e0 >> 5][e0 & 31] = a.b_ident ? ((e0 >> 5) == (e0 & 31) ? 1.0f : 0.0f) : pf_lb0;
-                LBt[e1 >> 5][e1 & 31] = a.b_ident ? ((e1 >> 5) == (e1 & 31) ? 1.0f : 0.0f) : pf_lb1;
-            }
-            float h0 = pf_h0, h1 = pf_h1;
-            float g0 = pf_g0, g1 = pf_g1;
-            // scales of the thread's two entries (one per row without GQ)
-            const float s0 = pf_s0, s1 = GQ ? pf_s1 : s0;
-            const float inv_s0 = (s0 > 0.0f) ? 1.0f / s0 : 0.0f;
-            const float inv_s1 = GQ ? ((s1 > 0.0f) ? 1.0f / s1 : 0.0f) : inv_s0;
             const int kc = a.b_ident ? 0 : (knear < I ? knear : I);   // column sources k = 1..kc
+            const bool has_next = I < I_last;
+            const int kc_next = a.b_ident ? 0 : (knear < I + 1 ? knear : I + 1);
+            const int slot = S_RING + (I % RING) * (TS * RSTR);
 
-            // multiplies source distance k of tile It into pacc (row or column kind)
-            auto pull_src = [&](int It, int k) {
-                f32x4 a0, a1, b0, b1;
+            // reads the operands of source distance k of tile It (row or column
+            // kind), to be multiplied into pacc
+            f32x4 a0, a1, b0, b1;
+            auto pull_read = [&](int It, int k) {
                 if (roww) {
-                    a0 = lds_chunk(LAs[k - 1], ra, 2 * ks);
-                    a1 = lds_chunk(LAs[k - 1], ra, 2 * ks + 1);
-                    b0 = lds_chunk(Yn[k - 2], rb, 2 * ks);
-                    b1 = lds_chunk(Yn[k - 2], rb, 2 * ks + 1);
+                    const float* la = sm + S_LA + (k - 1) * TILE_ELEMS;
+                    const float* y = sm + S_Y + (k - 2) * TILE_ELEMS;
+                    a0 = lds_chunk(la, ra, 2 * ks);
+                    a1 = lds_chunk(la, ra, 2 * ks + 1);
+                    b0 = lds_chunk(y, rb, 2 * ks);
+                    b1 = lds_chunk(y, rb, 2 * ks + 1);
                 } else {
-                    const float* e = &Ering[(It - k) % RING][rb][8 * ks];
-                    a0 = lds_chunk(LBn[k - 1], ra, 2 * ks);
-                    a1 = lds_chunk(LBn[k - 1], ra, 2 * ks + 1);
+                    const float* lb = sm + S_LB + (k - 1) * TILE_ELEMS;
+                    const float* e = sm + S_RING + ((It - k) % RING) * (TS * RSTR) + rb * RSTR + 8 * ks;
+                    a0 = lds_chunk(lb, ra, 2 * ks);
+                    a1 = lds_chunk(lb, ra, 2 * ks + 1);
                     b0 = *reinterpret_cast<const f32x4*>(e);
                     b1 = *reinterpret_cast<const f32x4*>(e + 4);
                 }
-                mfma_8(a0, a1, b0, b1, pacc);
             };
-            // issues the direct loads of tile It's operands: L^B[It, It-k],
-            // k = 1..min(knear, It), and F[It, J-k], k = 2..kr
-            auto stage = [&](int It, bool lb, bool y) {
-                const int nlb = lb ? (knear < It ? knear : It) : 0;
-                const int lim = 4 * (nlb + (y ? kr - 1 : 0));
-                // wave w issues row groups g = w, w + 8, ... (uniform control flow)
+            // hands the entries of group g of this wave's block to the solver
+            const int pd = ra0 + 4 * ks + rb;   // anti-diagonal of the lane's first entry
+            float* const pb = sm + S_BASE + pd * 64 + (roww ? TS + rb : ra0 + 4 * ks);
+            const int pstep = roww ? 64 : 65;   // the next entry is on the next anti-diagonal (column kind: and row)
+            auto put = [&](int g, f32x4 v) {
+                float* const b = pb - ((g >> 1) * 2 * SG) * 64;   // group g at parity g & 1
 #pragma unroll
-                for (int i = 0; i < (4 * (2 * KNEAR_MAX - 1) + 7) / 8; ++i) {
-                    const int g = w + 8 * i;
-                    if (g < lim) {
-                        const int ti = g >> 2;
-                        if (ti < nlb)
-                            stage_rows<0>(a.LB + packed_tile_offset(It, It - 1 - ti), LBn[ti], g & 3, l);
-                        else
-                            stage_rows<CPOL_SC1>(a.Y + ws_tile_offset(It, J - 2 - (ti - nlb), a.nt),
-                                                 Yn[ti - nlb], g & 3, l);
-                    }
+                for (int r = 0; r < 4; ++r)
+                    if ((unsigned)(pd + r - g * SG) < (unsigned)SG) b[r * pstep] = v[r];
+            };
+            // service wave 0: stores rows 16 h .. + 15 of F (device-coherent, whole
+            // rows); sets the tile's flag once its stores are complete; copies E to X
+            auto publish = [&](int It, int h) {
+                const __amdgpu_buffer_rsrc_t yr = tile_rsrc(a.Y + ws_tile_offset(It, J, a.nt));
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    const int r = 16 * h + 8 * j + (l >> 3), c = 4 * (l & 7);
+                    const f32x4 v = *reinterpret_cast<const f32x4*>(&sm[S_F + r * RSTR + c]);
+                    __builtin_amdgcn_raw_buffer_store_b128(v, yr, (r * TS + c) * 4, 0, CPOL_SC1);
+                }
+            };
+            auto publish_flag = [&](int It, int level) {
+                __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): the stores are complete
+                __atomic_signal_fence(__ATOMIC_SEQ_CST);
+                if (l == 0)
+                    __hip_atomic_store(a.flags + It * a.nt + J, level, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            };
+            auto e_to_x = [&](int It) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int r = 8 * j + (l >> 3), c = 4 * (l & 7);
+                    *reinterpret_cast<f32x4*>(a.X + ws_tile_offset(It, J, a.nt) + r * TS + c) =
+                        *reinterpret_cast<const f32x4*>(&sm[S_RING + (It % RING) * (TS * RSTR) + r * RSTR + c]);
                 }
             };
 
-            // 1. pull.  Operands not staged during the previous tile's loop
-            // (first tile of the strip, or a left strip that was late) are
-            // staged now.
-            const bool lb_need = !a.b_ident && kc >= 1;
-            if ((lb_need && !lb_staged) || (need_y && !y_staged)) {   // uniform
-                if (need_y && !y_staged) wait_ready(a.flags + I * a.nt + (J - 2), a.status, a.spin_limit);
-                stage(I, lb_need && !lb_staged, need_y && !y_staged);
+            // 1. pull.  Row operands that were not ready during the previous
+            // tile (a left strip that was late) are staged now.
+            if (need_y && !(y2 && (y3 || kr < 3))) {   // uniform
+                wait_ready(a.flags + I * a.nt + (J - 2), 2, a.status, a.spin_limit);
+                for (int k = 2; k <= (y3 ? 2 : kr); ++k)
+                    if (k > 2 || !y2) stage_y(I, k, w < 4 ? w : 4, 4);
                 __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): this wave's direct loads landed
-                __syncthreads();
+                seg_sync();
             }
-            {
-                const int kmax = roww ? kr : kc;
-                for (; nk <= kmax; ++nk) pull_src(I, nk);
+            f32x4 base = {0.0f, 0.0f, 0.0f, 0.0f}, far = base;
+            float s = 0.0f, inv_s = 0.0f;
+            float so[2][GQ ? 4 : 1];
+            // the wave's block of the tile's sums: distance 1, then the inputs
+            auto finish_base = [&]() {
                 if (roww) {
-                    if (kr >= 1) {   // distance 1: F[I, J-1] straight from memory after its flag
-                        wait_ready(a.flags + I * a.nt + (J - 1), a.status, a.spin_limit);
+                    if (kr >= 1) {   // F[I, J-1] straight from memory after its flag (1: rows 0 .. 15 published)
+                        wait_ready(a.flags + I * a.nt + (J - 1), rb0 ? 2 : 1, a.status, a.spin_limit);
                         const __amdgpu_buffer_rsrc_t r1 = tile_rsrc(a.Y + ws_tile_offset(I, J - 1, a.nt));
-                        const f32x4 b0 = __builtin_amdgcn_raw_buffer_load_b128(r1, (rb * TS + 8 * ks) * 4, 0, CPOL_SC1);
-                        const f32x4 b1 = __builtin_amdgcn_raw_buffer_load_b128(r1, (rb * TS + 8 * ks + 4) * 4, 0, CPOL_SC1);
-                        mfma_8(lds_chunk(LAs[0], ra, 2 * ks), lds_chunk(LAs[0], ra, 2 * ks + 1), b0, b1, pacc);
+                        const f32x4 b0 = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r1, (rb * TS + 8 * ks) * 4, 0, CPOL_SC1));
+                        const f32x4 b1 = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r1, (rb * TS + 8 * ks + 4) * 4, 0, CPOL_SC1));
+                        mfma_8(lds_chunk(sm + S_LA, ra, 2 * ks), lds_chunk(sm + S_LA, ra, 2 * ks + 1), b0, b1, pacc);
                     }
-                } else if (kc >= 1) {   // distance 1: E[I-1, J] from the ring
-                    const float* e = &Ering[(I - 1) % RING][rb][8 * ks];
-                    mfma_8(lds_chunk(LBn[0], ra, 2 * ks), lds_chunk(LBn[0], ra, 2 * ks + 1),
-                           *reinterpret_cast<const f32x4*>(e), *reinterpret_cast<const f32x4*>(e + 4), pacc);
+                } else {
+                    if (kc >= 1) {   // E[I-1, J] from the ring
+                        const float* e = sm + S_RING + ((I - 1) % RING) * (TS * RSTR) + rb * RSTR + 8 * ks;
+                        mfma_8(lds_chunk(sm + S_LB, ra, 2 * ks), lds_chunk(sm + S_LB, ra, 2 * ks + 1),
+                               *reinterpret_cast<const f32x4*>(e), *reinterpret_cast<const f32x4*>(e + 4), pacc);
+                    }
+                    lf0 = pfl0;
+                    lf1 = pfl1;
                 }
-                float (*out)[TS + 1] = roww ? HR : GC;
 #pragma unroll
-                for (int r = 0; r < 4; ++r) out[ra0 + 4 * ks + r][rb] = pacc[r];
-            }
-            if (tid == 0)   // can the next tile's row operands be staged during this tile's loop?
-                ynext = (need_y && I < I_last)
-                            ? __hip_atomic_load(a.flags + (I + 1) * a.nt + (J - 2), __ATOMIC_RELAXED,
-                                                __HIP_MEMORY_SCOPE_AGENT)
-                            : 0;
-            __syncthreads();
-            h0 += HR[q0][p];
-            h1 += HR[q1][p];
-            g0 += GC[p][q0];
-            g1 += GC[p][q1];
-            pacc = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-            nk = 2;
-            const bool has_next = I < I_last;
-            const int kc_next = a.b_ident ? 0 : (knear < I + 1 ? knear : I + 1);
-            lb_staged = has_next;
-            y_staged = has_next && ynext != 0;
-            if (has_next) {
-                __atomic_signal_fence(__ATOMIC_SEQ_CST);   // the F loads stay after the flag test
-                stage(I + 1, !a.b_ident && kc_next >= 1, y_staged);
-            }
-            const int kmax_next = roww ? (y_staged ? kr : 1) : kc_next;
-
-            if (has_next) {   // prefetch the next tile's inputs (consumed after the loop)
-                const int In = I + 1;
-                const int64_t tb = ws_tile_offset(In, J, a.nt);
-                const float* lbp = a.LB + packed_tile_offset(In, In);
-                if (!a.b_ident) {
-                    pf_lb0 = lbp[tid];
-                    pf_lb1 = lbp[tid + 512];
-                }
-                pf_h0 = a.X[tb + q0 * TS + p];
-                pf_h1 = a.X[tb + q1 * TS + p];
-                pf_g0 = a.Y[tb + p * TS + q0];
-                pf_g1 = a.Y[tb + p * TS + q1];
-                const int rn = In * TS + p;
-                pf_s0 = row_scale_of<GQ>(a.q, rn, cs0, a.m);
-                if (GQ) pf_s1 = row_scale_of<GQ>(a.q, rn, cs1, a.m);
-            }
-
-            float lbr[TS], lar0[TS], lar1[TS];
-#pragma unroll
-            for (int k = 0; k < TS; ++k) { lbr[k] = LBt[p][(k - q0) & 31]; lar0[k] = LAt[q0][(k - p) & 31]; lar1[k] = LAt[q1][(k - p) & 31]; }
-
-            // 2. in-tile rounding.  Quantisation without branches: a zero scale
-            // gives inv_s = 0, so x = 0, code 0, V = 0 and E = -W~ (the entry's
-            // alphabet is {0}).  Each thread keeps E, F and x of its own two
-            // entries when it processes them.
-            float eo0 = 0.0f, eo1 = 0.0f, fo0 = 0.0f, fo1 = 0.0f, xv0 = 0.0f, xv1 = 0.0f;
-            // one round: the active half-wave quantises anti-diagonals d and d + 1
-            // and broadcasts their E (per column) and F (per row) through LDS
-            auto round = [&](int kp, int d, int tp, int rb) {
-                const bool act = hf == ((kp >> 1) & 1);
-                // slot 0: anti-diagonal d
-                const bool v0 = act && (p + q0 == d);
-                const float acc0 = g0 + h0;
-                const float x0 = acc0 * inv_s0;
-                const float r0 = __builtin_amdgcn_fmed3f(rintf(x0), qlo, qhi);
-                const float ew0 = fmaf(r0, s0, -acc0);
-                const float e0 = v0 ? ew0 : 0.0f;
-                const float f0 = v0 ? g0 + ew0 : 0.0f;
-                // slot 1: anti-diagonal d + 1, plus the two pushes from d
-                const float eup = __int_as_float(
-                    __builtin_amdgcn_update_dpp(0, __float_as_int(e0), 0x138, 0xf, 0xf, true));
-                const float g1n = fmaf(lbr[(kp - 1) & 31], eup, g1);
-                const float h1n = fmaf(f0, lar1[kp & 31], h1);
-                const bool v1 = act && (p + q1 == d + 1);
-                const float acc1 = g1n + h1n;
-                const float x1 = acc1 * inv_s1;
-                const float r1 = __builtin_amdgcn_fmed3f(rintf(x1), qlo, qhi);
-                const float ew1 = fmaf(r1, s1, -acc1);
-                const float e1 = v1 ? ew1 : 0.0f;
-                const float f1 = v1 ? g1n + ew1 : 0.0f;
-                // broadcast (the inactive half writes the dummy slots)
-                Ecs[tp][rb][0][act ? q0 : TS + p] = e0;
-                Ecs[tp][rb][1][act ? q1 : TS + p] = e1;
-                Frs[tp][rb][act ? p : TS + p] = make_float2(f0, f1);
-                // keep the processed entries' outputs
-                eo0 = v0 ? e0 : eo0;
-                fo0 = v0 ? f0 : fo0;
-                xv0 = v0 ? x0 : xv0;
-                eo1 = v1 ? e1 : eo1;
-                fo1 = v1 ? f1 : fo1;
-                xv1 = v1 ? x1 : xv1;
+                for (int r = 0; r < 4; ++r) base[r] = pfx[r] + pacc[r];
+                pacc = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+                nk = !has_next ? 0 : roww ? kr : kc_next;
             };
-            // every thread adds the pushes of one round to both of its entries
-            auto update = [&](int kp, int tp, int rb) {
-                const float ea0 = Ecs[tp][rb][0][q0], ea1 = Ecs[tp][rb][0][q1];
-                const float eb0 = Ecs[tp][rb][1][q0], eb1 = Ecs[tp][rb][1][q1];
-                const float2 fr = Frs[tp][rb][p];
-                g0 = fmaf(lbr[kp & 31], ea0, g0);
-                g0 = fmaf(lbr[(kp + 1) & 31], eb0, g0);
-                g1 = fmaf(lbr[(kp - 1) & 31], ea1, g1);
-                g1 = fmaf(lbr[kp & 31], eb1, g1);
-                h0 = fmaf(fr.x, lar0[kp & 31], h0);
-                h0 = fmaf(fr.y, lar0[(kp + 1) & 31], h0);
-                h1 = fmaf(fr.x, lar1[kp & 31], h1);
-                h1 = fmaf(fr.y, lar1[(kp + 1) & 31], h1);
-            };
-            // Wave kq owns anti-diagonals 4kq .. 4kq + 3 (mod 32): two rounds in a
-            // row (its half 0, then its half 1).  Between them only that wave
-            // needs the first round's values, so it reads them back itself (LDS
-            // operations of one wave complete in order) and the workgroup
-            // barrier comes once per turn of two rounds.  Buffers alternate
-            // with the turn's parity, so a turn never overwrites values that a
-            // slower wave may still be reading from the previous turn.
-            // After the barrier of a turn, every wave except the one that is
-            // active in the next turn multiplies one staged pull source of the
-            // next tile (from turn PULL_T0 on, once the direct loads issued
-            // before the loop have landed).
-            for (int d0 = 0; d0 < 2 * TS; d0 += TS) {
-#pragma unroll
-                for (int kq = 0; kq < 8; ++kq) {
-                    const int tp = kq & 1, kpa = 4 * kq, kpb = 4 * kq + 2;
-                    const int turn = (d0 >> 2) + kq;
-                    if (w == kq) {                       // wave-uniform
-                        round(kpa, d0 + kpa, tp, 0);
-                        __builtin_amdgcn_wave_barrier();
-                        update(kpa, tp, 0);
-                        round(kpb, d0 + kpb, tp, 1);
-                    }
-                    __syncthreads();
-                    if (w != kq) update(kpa, tp, 0);
-                    update(kpb, tp, 1);
-                    if (turn == PULL_T0 - 1) __builtin_amdgcn_s_waitcnt(0x0F70);   // staged operands landed
-                    if (turn >= PULL_T0 && w != ((kq + 1) & 7) && nk <= kmax_next) {
-                        pull_src(I + 1, nk);
-                        ++nk;
-                    }
+            if (pull) {
+                for (; nk >= 2; --nk) {
+                    pull_read(I, nk);
+                    mfma_8(a0, a1, b0, b1, pacc);
                 }
-            }
-
-            // 3. publish F (device-coherent, whole rows), then the flag; E to the ring and X
-            Fst[p][q0] = fo0;
-            Fst[p][q1] = fo1;
-            Xg[q0 * TS + p] = eo0;
-            Xg[q1 * TS + p] = eo1;
-            Ering[I % RING][q0][p] = eo0;
-            Ering[I % RING][q1][p] = eo1;
-            __syncthreads();
-            if (w < 4) {   // wave w stores rows 8w .. 8w + 7, 16 bytes per lane
-                const int r = 8 * w + (l >> 3), c = l & 7;
-                const f32x4 v = *reinterpret_cast<const f32x4*>(&Fst[r][4 * c]);
-                __builtin_amdgcn_raw_buffer_store_b128(v, tile_rsrc(Yg), (r * TS + 4 * c) * 4, 0, CPOL_SC1);
-            }
-            __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): this wave's stores are complete
-            __syncthreads();
-            if (tid == 0)
-                __hip_atomic_store(a.flags + I * a.nt + J, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-
-            // 4. outputs, as whole row segments: every thread leaves x and the
-            // scale of its entries in LDS (F is stored, Fst is free), then 256
-            // threads write 4 consecutive entries of one row each (one 4-byte
-            // code store and 16-byte V and pre stores instead of 64 scattered
-            // rows per instruction)
-            Fst[p][q0] = xv0;
-            Fst[p][q1] = xv1;
-            if (GQ) {
-                So[p][q0] = s0;
-                So[p][q1] = s1;
+                if (lead) {
+                    finish_base();
+                    put(0, base);
+                    put(1, base);
+                }
+            } else if (solver) {
+                s = pfs;
+                inv_s = s > 0.0f ? 1.0f / s : 0.0f;   // zero scale: alphabet {0}
             } else {
-                So[0][p] = s0;
-            }
-            __syncthreads();
-            if (tid < 256) {
-                const float nan = __builtin_nanf("");
-                const int r = tid >> 3, cb = 4 * (tid & 7);
-                const int64_t orow = (int64_t)I * TS + r, ocol = (int64_t)J * TS + cb;
-                const f32x4 xq = *reinterpret_cast<const f32x4*>(&Fst[r][cb]);
-                float cv[4], vv[4], pv[4];
+                if (sv == 1) {
+                    float* t = sm + S_TB + p * TROW + 8 * hf;
 #pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const float sk = GQ ? So[r][cb + k] : So[0][r];
-                    cv[k] = __builtin_amdgcn_fmed3f(rintf(xq[k]), qlo, qhi);
-                    vv[k] = cv[k] * sk;
-                    pv[k] = sk > 0.0f ? xq[k] : nan;
+                    for (int j = 0; j < 8; ++j)
+                        if (8 * hf + j < NSRC) t[j] = pft[j];
                 }
-                if (orow < a.m) {
-                    const int64_t o = orow * a.n + ocol;
-                    if ((a.n & 3) == 0 && ocol + 3 < a.n) {   // aligned, inside the matrix
-                        uint32_t packed = 0;
+                if (sv >= 1) {
 #pragma unroll
-                        for (int k = 0; k < 4; ++k) packed |= (uint32_t)(uint8_t)(int8_t)(int)cv[k] << (8 * k);
-                        *reinterpret_cast<uint32_t*>(a.codes + o) = packed;
-                        *reinterpret_cast<f32x4*>(a.V + o) = f32x4{vv[0], vv[1], vv[2], vv[3]};
-                        if (a.pre) *reinterpret_cast<f32x4*>(a.pre + o) = f32x4{pv[0], pv[1], pv[2], pv[3]};
-                    } else {
+                    for (int j = 0; j < 2; ++j)
 #pragma unroll
-                        for (int k = 0; k < 4; ++k) {
-                            if (ocol + k < a.n) {
-                                a.codes[o + k] = (int8_t)(int)cv[k];
-                                a.V[o + k] = vv[k];
-                                if (a.pre) a.pre[o + k] = pv[k];
+                        for (int v = 0; v < (GQ ? 4 : 1); ++v) {
+                            so[j][v] = pfo[j][v];
+                            if (GQ) {
+                                const int e = S_SC + (r0 + 16 * j) * (TS + 1) + cb + v;
+                                sm[e] = so[j][v];
+                                sm[e + TS * (TS + 1)] = so[j][v] > 0.0f ? 1.0f / so[j][v] : 0.0f;
+                            }
+                        }
+                }
+            }
+            // can the next tile's row operands be staged?
+            auto poll = [&](int k) {
+                if (sv == 2 && l == 0)
+                    yready[k - 2] = kr < k || __hip_atomic_load(a.flags + (I + 1) * a.nt + (J - k), __ATOMIC_RELAXED,
+                                                                __HIP_MEMORY_SCOPE_AGENT) >= 2;
+            };
+            if (has_next) poll(3);
+            seg_sync();
+            y3 = has_next && yready[1] != 0;
+
+            // 2. the element anti-diagonals
+            float V[2 * SG];   // solver: E (column half) and F (row half) of the last 2 SG steps
+#pragma unroll
+            for (int k = 0; k < 2 * SG; ++k) V[k] = 0.0f;
+            // lane constants of the solver (byte addresses in LDS): the coefficient
+            // row (column half: fixed), E or F and x of the lane's entry
+            const uint32_t smb = (uint32_t)(uintptr_t)(lds_char*)sm;
+            const lds_char* cp = (const lds_char*)sm + 4 * (hf ? S_TA - p * TROW : S_TB + p * TROW);
+            const int cp_inc = hf ? 4 * TROW : 0;
+            uint32_t ea = smb + 4 * (hf ? S_F + p * (RSTR - 1) : slot - p * (RSTR - 1));
+            const uint32_t ea_inc = 4 * (hf ? 1 : RSTR);
+            uint32_t xa = smb + 4 * (S_X + p * (RSTR - 1));
+            // SG steps; H: which half of the history ring they fill
+            auto group = [&](auto H, int g) {
+                constexpr int N2 = 2 * SG, NC = 3;
+                float b[SG], es[GQ ? SG : 1], ei[GQ ? SG : 1];
+                f32x4 c[NC][NV];   // coefficients, two steps ahead
+                auto coef = [&](int r) {
+#pragma unroll
+                    for (int v = 0; v < NV; ++v) c[r % NC][v] = *(const lds_f32x4*)(cp + 16 * v);
+                    cp += cp_inc;
+                };
+                coef(0);
+                coef(1);
+#pragma unroll
+                for (int r = 0; r < SG; ++r) {
+                    b[r] = sm[S_BASE + ((g & 1) * SG + r) * 64 + l];
+                    if (GQ) {
+                        es[r] = sm[S_SC + p * TS + g * SG + r];   // entry (p, t - p); other rows' outside the tile
+                        ei[r] = sm[S_SC + TS * (TS + 1) + p * TS + g * SG + r];
+                    }
+                }
+#pragma unroll
+                for (int r = 0; r < SG; ++r) {
+                    const int u = H.value * SG + r;   // ring slot of this step
+                    if (r + 2 < SG) coef(r + 2);
+                    // the column half's history moves one row down: lane p gets the
+                    // errors of lane p - 1
+#pragma unroll
+                    for (int k = 1; k <= SG + r; ++k) {
+                        float& h = V[(u - k + N2) % N2];
+                        h = __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(h), __float_as_int(h),
+                                                                       0x138, 0x3, 0xf, true));
+                    }
+                    float x = b[r];
+#pragma unroll
+                    for (int k = NSRC; k >= 1; --k)
+                        if (k <= SG + r) x = fmaf(V[(u - k + N2) % N2], c[r % NC][(k - 1) >> 2][(k - 1) & 3], x);
+                    // G and H in both halves
+                    const auto gh = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+                    const float gs = __uint_as_float(gh[0]), hs = __uint_as_float(gh[1]);
+                    const float sr = GQ ? es[r] : s, ir = GQ ? ei[r] : inv_s;
+                    const float acc = gs + hs;
+                    const float xq = acc * ir;
+                    const float rq = __builtin_amdgcn_fmed3f(rintf(xq), qlo, qhi);
+                    const float e = fmaf(rq, sr, -acc);
+                    const float f = gs + e;
+                    // lanes with an entry on this anti-diagonal: max(0, t - 31) <= p <= min(t, 31)
+                    const uint64_t in = (0x1fffffffeull << (g * SG + r)) >> 32;
+                    float v = __builtin_amdgcn_inverse_ballot_w64(in) ? e : 0.0f;
+                    v = __builtin_amdgcn_inverse_ballot_w64(in << 32) ? f : v;
+                    V[u] = v;
+                    // E or F, and x (the same in both halves), of the lanes in the tile
+                    asm volatile("s_mov_b64 exec, %[m]\n\tds_write_b32 %[a], %[v]\n\t"
+                                 "ds_write_b32 %[b], %[x] offset:%[o]\n\ts_mov_b64 exec, -1"
+                                 :: [m] "s"(in | in << 32), [a] "v"(ea), [v] "v"(v), [b] "v"(xa), [x] "v"(xq),
+                                    [o] "i"(4 * r)
+                                 : "memory");
+                    ea += ea_inc;
+                }
+                xa += 4 * SG;
+            };
+            // the pull waves' part of group g: the pushes of group g - 1, complete
+            // since the last barrier, into the whole tile (older entries in the
+            // block are stale by then and not used), then the sums of group g + 1
+            auto push = [&](int g) {
+                // the block has entries on the anti-diagonals ra0 + rb0 .. + 30 only,
+                // its rows of the source tile on rb0 .. rb0 + 46 (all uniform)
+                if (g < 1 || g + 1 >= NGRP || ra0 + rb0 + TS - 2 < (g + 1) * SG) return;
+                if ((!roww && a.b_ident) || rb0 >= g * SG) {
+                    if (ra0 + rb0 < (g + 2) * SG) put(g + 1, base + far);
+                    return;
+                }
+                const float* src = sm + (roww ? S_F : slot) + rb * RSTR + 8 * ks;
+                f32x4 b0 = *reinterpret_cast<const f32x4*>(src), b1 = *reinterpret_cast<const f32x4*>(src + 4);
+                const int d0 = rb + 8 * ks - (g - 1) * SG;   // anti-diagonal of b0[0] within the group
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    b0[t] = (unsigned)(d0 + t) < (unsigned)SG ? b0[t] : 0.0f;
+                    b1[t] = (unsigned)(d0 + 4 + t) < (unsigned)SG ? b1[t] : 0.0f;
+                }
+                mfma_8(lf0, lf1, b0, b1, far);
+                if (ra0 + rb0 < (g + 2) * SG) put(g + 1, base + far);
+            };
+            auto others = [&](int g) {   // pull and service waves, beside group g of the solver
+                if (pull) {
+                    if (g == base_g) finish_base();
+                    // one source of the next tile per group, two in the last; its
+                    // operands are read before the pushes
+                    auto ready = [&]() {   // uniform
+                        return nk >= 2 && use_group(nk, !roww) <= g && (!roww || (y3 && (nk > 2 || y2)));
+                    };
+                    const bool one = ready();
+                    if (one) pull_read(I + 1, nk);
+                    push(g);
+                    if (g == 1 && has_next) prefetch(I + 1);
+                    if (one) {
+                        mfma_8(a0, a1, b0, b1, pacc);
+                        --nk;
+                        if (g + 1 == NGRP && ready()) {
+                            pull_read(I + 1, nk);
+                            mfma_8(a0, a1, b0, b1, pacc);
+                            --nk;
+                        }
+                    }
+                } else {
+                    if (g == 0 && sv == 0 && I > I_first) {   // the rest of the tile above
+                        publish_flag(I - 1, 2);
+                        e_to_x(I - 1);
+                    }
+                    if (has_next) {
+                        if (g == POLL_G) poll(2);
+                        __atomic_signal_fence(__ATOMIC_SEQ_CST);   // the F loads stay after the flag test
+                        if (g < use_group(2, true)) {
+                            if (g >= 1) __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): the last group's direct loads landed
+                            const int n = 3 * g + sv;             // stage_index of this wave's tile
+                            const int k = n == 14 ? 1 : KNEAR_MAX - (n >> 1);
+                            if (n <= 14) {
+                                if (n == 14 || (n & 1)) {
+                                    if (k <= kc_next) stage_lb(I + 1, k, 0, 1);
+                                } else if (k <= kr && y3 && (k > 2 || y2)) {
+                                    stage_y(I + 1, k, 0, 1);
+                                }
+                            }
+                            if (g == 1) prefetch(I + 1);
+                        }
+                    }
+                    if (g == PUB_G && sv == 0) {
+                        publish(I, 0);
+                        publish_flag(I, 1);
+                    }
+                }
+            };
+            if (solver && has_next) prefetch(I + 1);
+            for (int g = 0; g < NGRP; g += 2) {
+                if (solver) group(std::integral_constant<int, 0>{}, g);
+                else others(g);
+                seg_sync();
+                if (g == POLL_G) y2 = y3 && yready[0] != 0;
+                if (g + 1 < NGRP) {   // uniform
+                    if (solver) group(std::integral_constant<int, 1>{}, g + 1);
+                    else others(g + 1);
+                    seg_sync();
+                }
+            }
+
+            // 3. the rest of F, whose flag and the copy of E wait for the next
+            // tile's group 0; outputs
+            if (sv == 0) {
+                publish(I, 1);
+                if (!has_next) {
+                    publish_flag(I, 2);
+                    e_to_x(I);
+                }
+            } else if (sv >= 1) {
+                const float nan = __builtin_nanf("");
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    const int r = r0 + 16 * j;
+                    const int64_t orow = (int64_t)I * TS + r, ocol = (int64_t)J * TS + cb;
+                    const f32x4 xq = *reinterpret_cast<const f32x4*>(&sm[S_X + r * RSTR + cb]);
+                    float cv[4], vv[4], pv[4];
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        const float sk = so[j][GQ ? k : 0];
+                        cv[k] = __builtin_amdgcn_fmed3f(rintf(xq[k]), qlo, qhi);
+                        vv[k] = cv[k] * sk;
+                        pv[k] = sk > 0.0f ? xq[k] : nan;
+                    }
+                    if (orow < a.m) {
+                        const int64_t o = orow * a.n + ocol;
+                        if ((a.n & 3) == 0 && ocol + 3 < a.n) {   // aligned, inside the matrix
+                            uint32_t packed = 0;
+#pragma unroll
+                            for (int k = 0; k < 4; ++k) packed |= (uint32_t)(uint8_t)(int8_t)(int)cv[k] << (8 * k);
+                            *reinterpret_cast<uint32_t*>(a.codes + o) = packed;
+                            *reinterpret_cast<f32x4*>(a.V + o) = f32x4{vv[0], vv[1], vv[2], vv[3]};
+                            if (a.pre) *reinterpret_cast<f32x4*>(a.pre + o) = f32x4{pv[0], pv[1], pv[2], pv[3]};
+                        } else {
+#pragma unroll
+                            for (int k = 0; k < 4; ++k) {
+                                if (ocol + k < a.n) {
+                                    a.codes[o + k] = (int8_t)(int)cv[k];
+                                    a.V[o + k] = vv[k];
+                                    if (a.pre) a.pre[o + k] = pv[k];
+                                }
                             }
                         }
                     }
@@ -576,6 +710,18 @@ __global__ __launch_bounds__(512) void k_seg(SegArgs a) {
             }
         }
     }
+}
+
+// Wave i runs on SIMD i mod 4: the solver shares its SIMD with two service waves
+// only (beside pull waves its steps took a third longer).
+template <bool GQ, bool ASYM>
+__global__ __launch_bounds__(SEG_THREADS) void k_seg(SegArgs a) {
+    __shared__ __attribute__((aligned(16))) float sm[GQ ? S_END_GQ : S_END];
+    __shared__ int tk, yready[2];
+    const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    if (w == 0) seg_role<GQ, ASYM, SOLVER>(a, sm, tk, yready, w, 0);
+    else if (w == 4 || w == 8 || w == 11) seg_role<GQ, ASYM, SERVICE>(a, sm, tk, yready, w, w >> 2 == 1 ? 0 : w == 8 ? 1 : 2);
+    else seg_role<GQ, ASYM, PULL>(a, sm, tk, yready, w, w - 1 - (w > 4) - (w > 8));
 }
 
 // Fills n 32-bit words with v (a debug aid: poisoning the workspace before a
@@ -904,13 +1050,13 @@ hipError_t run_plan(hipStream_t st, hipStream_t side, const Plan& plan, const fl
                 const int grid = op.nstrips < SEG_GRID ? op.nstrips : SEG_GRID;
                 const bool gq = q.gsize > 0 || q.col_scale, asym = q.qlo != -q.qhi;
                 if (gq && asym)
-                    hipLaunchKernelGGL((k_seg<true, true>), dim3((unsigned)grid), dim3(512), 0, st, sa);
+                    hipLaunchKernelGGL((k_seg<true, true>), dim3((unsigned)grid), dim3(SEG_THREADS), 0, st, sa);
                 else if (gq)
-                    hipLaunchKernelGGL((k_seg<true, false>), dim3((unsigned)grid), dim3(512), 0, st, sa);
+                    hipLaunchKernelGGL((k_seg<true, false>), dim3((unsigned)grid), dim3(SEG_THREADS), 0, st, sa);
                 else if (asym)
-                    hipLaunchKernelGGL((k_seg<false, true>), dim3((unsigned)grid), dim3(512), 0, st, sa);
+                    hipLaunchKernelGGL((k_seg<false, true>), dim3((unsigned)grid), dim3(SEG_THREADS), 0, st, sa);
                 else
-                    hipLaunchKernelGGL((k_seg<false, false>), dim3((unsigned)grid), dim3(512), 0, st, sa);
+                    hipLaunchKernelGGL((k_seg<false, false>), dim3((unsigned)grid), dim3(SEG_THREADS), 0, st, sa);
             } else {
                 node(op, st);
             }
