@@ -161,8 +161,8 @@ bakron_status bakron_factor(const float *A, int64_t n, const float *B, int64_t m
  * such solves through the two-sided solver instead (same codes up to fp32
  * summation order).  Debug switches read at handle creation:
  * BAKRON_KNEAR=k (0..8) sets how many tile anti-diagonals a tile pulls from
- * itself instead of receiving them from node pushes; BAKRON_MACRO=4 or 2
- * forces 128 x 128 or 64 x 64 macro tiles in every node push;
+ * itself instead of receiving them from node pushes; BAKRON_MACRO=8, 4
+ * or 2 forces 256 x 256, 128 x 128 or 64 x 64 macro tiles in every node push;
  * BAKRON_GPTQ_RANGE=t (1..64) sets the one-sided range to t column tiles of
  * 32 (the tests use it to run several ranges on small shapes).
  */
@@ -288,7 +288,8 @@ bakron_status bakron_factor_export(const bakron_factors *f, int which, float *ds
  *   flops       algorithmic work: 2*32^3 flops per (source, target) tile pair
  *               fed back (Eq. (1)), plus the in-tile pairs of solved tiles;
  *               for class 0, bytes moved instead
- *   mfma_flops  flops executed on the matrix cores, zero-masked tiles included
+ *   mfma_flops  flops of the fp32 products executed on the matrix cores, zero-masked
+ *               tiles included (a node push executes six bf16 products for each)
  * Classes beyond nstats are dropped.  Returns BAKRON_EINVAL if no profiled
  * solve has been enqueued since enabling.
  */

@@ -54,7 +54,7 @@ struct bakron_factors {
     void* ws_mem = nullptr;         // X, Y tile arrays, flags, counters, status (bk::Workspace)
     bk::Workspace ws{};
     int knear = 8;
-    // node macro tile: 0 per node (default), 4 or 2 forced (BAKRON_MACRO)
+    // node macro tile: 0 per node (default), 8, 4 or 2 forced (BAKRON_MACRO)
     int macro = 0;
     // BAKRON_POISON=1 at creation: fill the workspace with NaN / -1 before
     // every solve (debug aid: the solve must never read a word it did not
@@ -210,19 +210,28 @@ static void leaves(int K, int L, int knear, std::vector<std::pair<int, int>>& ou
     leaves(Mid, L, knear, out);
 }
 
-// macro: 0 chooses the macro tile per node (128 x 128 when a node has at
-// least 1536 such items, three rounds of the 512 that the chip holds at
-// once, else 64 x 64: with fewer, the last round of 128 x 128 items leaves
-// most CUs idle); 4 or 2 forces one size
-static bool node_op(int K, int Mid, int tlo, int thi, int mt, int nt, int knear, int b_ident,
+// macro: 0 chooses the macro tile per push, the largest of 256 x 256, 128 x 128
+// and 64 x 64 with at least NODE_MIN_ITEMS items (a wider block reads its
+// operands less often and splits them for more products; with fewer items the
+// last round leaves most CUs idle); 8, 4 or 2 forces one size.
+// The nodes of at most NODE32_SPAN tile anti-diagonals go to the fp32 kernel.  The rule looks at the node, not at the push, so that the one- and
+// the two-stream plan, which cut a node's push differently, give the same bits.
+constexpr int NODE_MIN_ITEMS = 512;
+constexpr int NODE32_SPAN = 36;
+static bool node_op(int K, int Mid, int L, int tlo, int thi, int mt, int nt, int knear, int b_ident,
                     std::vector<int4>& items, bk::PlanOp& op, int macro) {
     const double T = bk::TS;
-    int MT = macro == 2 ? 2 : bk::MACRO;
+    const bool fp32 = macro == 0 && L - K <= NODE32_SPAN;
+    int MT = macro ? macro : fp32 ? 2 : 8;
     std::vector<int4> its;
     node_items(K, Mid, tlo, thi, mt, nt, knear, b_ident, MT, its);
-    if (macro == 0 && (int)its.size() < 1536) {
-        MT = 2;
-        node_items(K, Mid, tlo, thi, mt, nt, knear, b_ident, 2, its);
+    if (macro == 0 && !fp32 && (int)its.size() < NODE_MIN_ITEMS) {
+        MT = 4;
+        node_items(K, Mid, tlo, thi, mt, nt, knear, b_ident, MT, its);
+        if ((int)its.size() < NODE_MIN_ITEMS) {
+            MT = 2;
+            node_items(K, Mid, tlo, thi, mt, nt, knear, b_ident, MT, its);
+        }
     }
     if (its.empty()) return false;
     op = bk::PlanOp{};
@@ -233,6 +242,7 @@ static bool node_op(int K, int Mid, int tlo, int thi, int mt, int nt, int knear,
     op.tlo = tlo;
     op.thi = thi;
     op.macro = MT;
+    op.fp32 = fp32;
     op.item_off = (int)items.size();
     op.item_cnt = (int)its.size();
     op.rel = -1;
@@ -281,11 +291,11 @@ static void build_ops(int K, int L, int mt, int nt, int knear, int b_ident, bool
     std::vector<std::pair<int, int>> right;
     leaves(Mid, L, knear, right);
     bk::PlanOp op;
-    if (node_op(K, Mid, Mid, defer ? right[0].second : L, mt, nt, knear, b_ident, items, op, macro))
+    if (node_op(K, Mid, L, Mid, defer ? right[0].second : L, mt, nt, knear, b_ident, items, op, macro))
         plan.ops.push_back(op);
     if (defer)
         for (size_t j = 1; j < right.size(); ++j)
-            if (node_op(K, Mid, right[j].first, right[j].second, mt, nt, knear, b_ident, items, op,
+            if (node_op(K, Mid, L, right[j].first, right[j].second, mt, nt, knear, b_ident, items, op,
                         macro)) {
                 op.rel = rel;
                 plan.side.push_back(op);
@@ -355,7 +365,7 @@ extern "C" bakron_status bakron_factor(const float* A, int64_t n, const float* B
     }
     if (const char* mc = std::getenv("BAKRON_MACRO")) {
         int v = std::atoi(mc);
-        if (v == 2 || v == 4) f->macro = v;
+        if (v == 2 || v == 4 || v == 8) f->macro = v;
     }
 
     // A and B are factored concurrently (their block steps are latency-bound):

@@ -13,8 +13,6 @@ namespace bk {
 // only on tiles (I', J') with I' <= I, J' <= J.
 constexpr int TS = 32;
 constexpr int TILE_ELEMS = TS * TS;
-// Node products use MACRO x MACRO solver tiles per workgroup (128 x 128).
-constexpr int MACRO = 4;
 // Largest supported near-field distance (tiles pulled by the target).
 constexpr int KNEAR_MAX = 8;
 
@@ -61,7 +59,8 @@ struct PlanOp {
     int strip_lo;        // segment: first tile column (strip) with a tile in [K, L)
     int nstrips;         // segment: number of such strips
     int counter;         // segment: index of its ticket counter
-    int macro;           // node: solver tiles per workgroup edge (4 or 2)
+    int macro;           // node: solver tiles per workgroup edge (8, 4 or 2)
+    int fp32;            // node: pushed on fp32 MFMA (short source ranges; macro 2)
     int item_off, item_cnt;
     int rel;             // side op: main op after which it may start
     int rec_rel;         // main op: some side op waits for it (record its event)

@@ -35,6 +35,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "split.h"
 
 #include <vector>
 
@@ -769,31 +770,118 @@ struct NodeArgs {
     const int4* items;  // work list of this launch (see NodeItem in common.h)
 };
 
-// Band push of one divide-and-conquer node on fp32 MFMA.
+// Band push of one divide-and-conquer node, on the bf16 matrix cores with every
+// fp32 operand split in three (split.h).
 //
 // Both pushes are computed as C[M][N] += sum_k A[M][k] * B[N][k] over source
-// tiles kt (K chunks of TS), with every operand tile stored [row][k]:
+// tiles kt (TS k's each, two chunks), with every operand tile stored [row][k]:
 //   column push: C = Y[I, J] (row-major), A = L^B[I, kt], B = E[kt, J] read
 //                from X, whose tiles are column-major (= E^T);
 //   row push:    C = X[I, J] stored column-major, i.e. C^T[J][I]
 //                = sum L^A[J, kt] * F[I, kt]^T, A = L^A[J, kt], B = F[I, kt]
 //                read from Y (row-major).
-// So every global -> LDS copy is a straight 16-byte copy and every output
-// write is coalesced.  A workgroup computes MT x MT solver tiles with 4 waves
-// in a 2 x 2 arrangement (each wave MT/2 x MT/2 blocks of
-// v_mfma_f32_32x32x2f32).  Inside a K chunk the 32 k's are split between the
-// two lane halves (half h takes k = 16h + s at step s), so each lane reads 16
-// consecutive floats per operand with four 16-byte LDS loads.  LDS is double
-// buffered and the chunks two ahead are prefetched into registers while the
-// current one is multiplied.  The (source, target) validity masks are separable, so
+// So every operand read is a 16-byte piece of a tile row and every output
+// write is coalesced.  The (source, target) validity masks are separable, so
 // invalid source tiles are staged as zeros and the sums stay exact.
 //
-// One workgroup per work-list item: the host lists only items with a
-// non-empty source range, longest first, so the long K loops start early.
-constexpr int LDS_STRIDE = TS + 4;   // 36 floats: 16-byte rows, no b128 bank conflicts
+// One workgroup per work-list item (MT x MT solver tiles): the host lists only
+// items with a non-empty source range, longest first, so the long K loops
+// start early.  Bound by the matrix cores and the power they draw on the large
+// nodes; measured against the fp32 MFMA kernel before it: all pushes of the
+// 28672 x 8192 layer 65.0 -> 53.0 ms (129 -> 159 TFLOP/s of fp32 products), of
+// 11008 x 4096 5.6 -> 5.0.
 template <int MT>
-__global__ __launch_bounds__(256, (MT == 4 ? 2 : 4)) void k_node(NodeArgs a) {
-    constexpr int WB = MT / 2;       // 32x32 blocks per wave per dimension
+__global__ __launch_bounds__(SplitShape<MT>::TH, (MT == 2 ? 4 : 2)) void k_node(NodeArgs a) {
+    using C = SplitShape<MT>;
+    __shared__ __attribute__((aligned(16))) uint16_t S[C::LDS];
+    const int4 it = a.items[blockIdx.x];
+    const int I0 = it.x, J0 = it.y;
+    const bool colpush = (it.z & 1) == 0;
+    const int klo = it.z >> 1, khi = it.w;
+
+    const int tid = threadIdx.x;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63;
+    const int wm = wv / C::WN, wn = wv % C::WN;
+
+    // Operand tile of K tile kt as a buffer resource: a valid tile covers its
+    // 4 KB, an invalid one (outside the matrix, outside the (source, target)
+    // masks or past the item's range) has no records, so its loads return
+    // zeros without touching memory.  Every chunk therefore issues the same
+    // loads unconditionally, which lets the compiler wait only for the chunk
+    // it stores.  A wave stages rows of one operand and, per pass, of one
+    // tile, so base, stride and range are wave-uniform; consecutive K tiles
+    // sit a fixed stride apart.
+    //   column push: A = L^B[I0 + t, kt] (kt <= I - knear - 1), B = E[kt, J0 + t]
+    //                (kt + J in [K, Mid)), read from X;
+    //   row push:    A = L^A[J0 + t, kt] (kt <= J - knear - 1), B = F[I0 + t, kt]
+    //                (I + kt in [K, Mid)), read from Y.
+    const bool opb = wv >= C::TH / 128;
+    const int th = tid & (C::TH / 2 - 1);
+    const float* base[C::NU];
+    int lo[C::NU], hi[C::NU];
+    const int64_t stride = opb && colpush ? (int64_t)a.nt * TILE_ELEMS : TILE_ELEMS;
+#pragma unroll
+    for (int u = 0; u < C::NU; ++u) {
+        const int t = u * (C::RP / TS) + __builtin_amdgcn_readfirstlane(th >> 7);
+        if (!opb) {
+            const int Ia = colpush ? I0 + t : J0 + t;   // factor tile row
+            const bool in = colpush ? Ia < a.mt : Ia < a.nt;
+            base[u] = in ? (colpush ? a.LB : a.LA) + packed_tile_offset(Ia, 0) : a.LA;
+            lo[u] = 0;
+            hi[u] = in ? min(khi, Ia - a.knear) : 0;
+        } else {
+            const int Ib = colpush ? J0 + t : I0 + t;   // fixed coordinate of the source tile
+            const bool in = colpush ? Ib < a.nt : Ib < a.mt;
+            base[u] = in ? (colpush ? a.X + ws_tile_offset(0, Ib, a.nt) : a.Y + ws_tile_offset(Ib, 0, a.nt))
+                         : a.LA;
+            lo[u] = max(a.K - Ib, 0);
+            hi[u] = in ? min(khi, a.Mid - Ib) : 0;
+        }
+    }
+    const int voff = (((th >> 2) & (TS - 1)) * TS + 4 * (th & 3)) * 4;
+    f32x16 acc[C::WX][C::WY];
+    split_gemm<MT>(S, 2 * (khi - klo), tid, [&](int c, int u) {
+        // (an invalid tile's address may lie outside every allocation: with no
+        // records nothing is read)
+        const int kt = klo + (c >> 1);
+        const int nrec = (kt >= lo[u] && kt < hi[u]) ? TILE_ELEMS * 4 : 0;
+        const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<float*>(base[u] + kt * stride), (short)0, nrec, 0x00020000);
+        return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, voff, (c & 1) * 64, 0));
+    }, acc);
+
+    // epilogue: block (x, y) of wave (wm, wn) is output solver tile
+    // (M tile wm*WX+x, N tile wn*WY+y); C[M][N] row-major inside the tile.
+    const int lr = l & 31, lk = l >> 5;
+#pragma unroll
+    for (int x = 0; x < C::WX; ++x)
+#pragma unroll
+        for (int y = 0; y < C::WY; ++y) {
+            const int tm = wm * C::WX + x, tn = wn * C::WY + y;
+            const int I = colpush ? I0 + tm : I0 + tn;
+            const int J = colpush ? J0 + tn : J0 + tm;
+            if (I >= a.mt || J >= a.nt || I + J < a.tlo || I + J >= a.thi) continue;
+            float* out = (colpush ? a.Y : a.X) + ws_tile_offset(I, J, a.nt);
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int rr = (r >> 2) * 8 + lk * 4 + (r & 3);
+                out[rr * TS + lr] += acc[x][y][r];
+            }
+        }
+}
+
+// The same push on fp32 MFMA, 64 x 64 per workgroup: for the nodes of at most
+// NODE32_SPAN tile anti-diagonals.  Their source ranges are so short that the
+// launch is bound by latency and operand bytes; the split's conversions only
+// add to it (a launch of the 18-diagonal nodes of the 1024 x 1024 layer takes
+// 13 us here, 15 with k_node<2>).  4 waves in a 2 x 2 arrangement; inside a K chunk
+// the 32 k's are split between the two lane halves (half h takes k = 16h + s at
+// step s), so each lane reads 16 consecutive floats per operand with four
+// 16-byte LDS loads.  LDS is double buffered and the chunks two ahead are
+// prefetched into registers while the current one is multiplied.
+constexpr int LDS_STRIDE = TS + 4;   // 36 floats: 16-byte rows, no b128 bank conflicts
+__global__ __launch_bounds__(256, 4) void k_node32(NodeArgs a) {
+    constexpr int MT = 2, WB = MT / 2;   // 64 x 64 per workgroup, one 32x32 block per wave
     __shared__ __attribute__((aligned(16))) float As[2][MT * TS][LDS_STRIDE];
     __shared__ __attribute__((aligned(16))) float Bs[2][MT * TS][LDS_STRIDE];
     const int4 it = a.items[blockIdx.x];
@@ -1027,10 +1115,15 @@ hipError_t run_plan(hipStream_t st, hipStream_t side, const Plan& plan, const fl
         nd.tlo = op.tlo;
         nd.thi = op.thi;
         nd.items = items + op.item_off;
-        if (op.macro == 4)
-            hipLaunchKernelGGL(k_node<4>, dim3((unsigned)op.item_cnt), dim3(256), 0, s, nd);
+        const dim3 grid((unsigned)op.item_cnt);
+        if (op.macro == 8)
+            hipLaunchKernelGGL(k_node<8>, grid, dim3(SplitShape<8>::TH), 0, s, nd);
+        else if (op.fp32)
+            hipLaunchKernelGGL(k_node32, grid, dim3(256), 0, s, nd);
+        else if (op.macro == 4)
+            hipLaunchKernelGGL(k_node<4>, grid, dim3(SplitShape<4>::TH), 0, s, nd);
         else
-            hipLaunchKernelGGL(k_node<2>, dim3((unsigned)op.item_cnt), dim3(256), 0, s, nd);
+            hipLaunchKernelGGL(k_node<2>, grid, dim3(SplitShape<2>::TH), 0, s, nd);
     };
     int waited_side = 0, waited_rel = -1;
     for (const std::pair<int, int>& o : plan.order) {

@@ -97,11 +97,94 @@ __device__ inline void split_mma(const uint16_t* a, const uint16_t* b, int plane
                 c += t[(i - 1) & 1];
                 asm volatile("" : "+v"(c));   // add here: t must not stay live
             }
-            __builtin_amdgcn_sched_barrier(0);
+            if (WX * WY > 1) __builtin_amdgcn_sched_barrier(0);
         }
     }
     acc[WX - 1][WY - 1] += t[(WX * WY - 1) & 1];
     asm volatile("" : "+v"(acc[WX - 1][WY - 1]));
+}
+
+// A product of MT x MT solver tiles (MT * 32 rows of A times MT * 32 rows of B,
+// both with k contiguous), the whole pipeline of one workgroup:
+//   MT = 8: 8 waves of 128 x 64, 144 KiB of LDS, one workgroup per CU;
+//   MT = 4: 4 waves of 64 x 64, two workgroups per CU;
+//   MT = 2: 4 waves of 32 x 32, four workgroups per CU.
+// Half of the threads stage A, half B: per chunk of 16 k's a thread converts
+// four k's of NU rows.  LDS is double-buffered and NS chunks are in flight in
+// registers behind the one being stored, so a global load has NS chunks of
+// MFMA work to hide behind (one is enough at MT = 8, where a chunk takes
+// 1.3 us or more).  The chunk sums and their order do not depend on MT: every
+// entry gets the same bits from all three sizes (chunks of zeros add nothing).
+template <int MT>
+struct SplitShape {
+    static constexpr int WX = MT == 8 ? 4 : MT == 4 ? 2 : 1, WY = MT >= 4 ? 2 : 1;   // blocks per wave
+    static constexpr int WN = MT / WY;                    // waves along B
+    static constexpr int TH = 64 * (MT / WX) * WN;        // threads
+    static constexpr int RP = TH / 8;                     // rows staged per pass (4 threads per row)
+    static constexpr int NU = MT * TS / RP;               // passes
+    static constexpr int CB = MT == 2 ? 2 : 1;            // chunks per step (one barrier each)
+    static constexpr int NS = MT == 8 ? 1 : MT == 4 ? 4 : 3;   // steps in flight
+    static constexpr int PLANE = 2 * MT * TS * SPROW;     // rows of A, then rows of B
+    static constexpr int LDS = 2 * CB * 3 * PLANE;             // bf16 slots
+};
+
+// load(c, u): the thread's four k's, 16 c + 4 (tid & 3) .. + 3, of row
+// ((tid mod TH/2) >> 2) + u RP of A (first half of the threads) or B; past the
+// last chunk it may return anything (never stored).
+template <int MT, class Load>
+__device__ inline void split_gemm(uint16_t* S, int nch, int tid, Load load,
+                                  f32x16 (&acc)[SplitShape<MT>::WX][SplitShape<MT>::WY]) {
+    using C = SplitShape<MT>;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63;
+    const int wm = wv / C::WN, wn = wv % C::WN;
+    const int op = wv >= C::TH / 128, t = tid & (C::TH / 2 - 1);
+    uint16_t* const dst = S + (op * MT * TS + (t >> 2)) * SPROW + 4 * (t & 3);
+    const uint16_t* const fa = S + wm * C::WX * TS * SPROW;
+    const uint16_t* const fb = S + (MT * TS + wn * C::WY * TS) * SPROW;
+    f32x4 r[C::NS][C::CB][C::NU];
+    auto fetch = [&](int step, int s) {
+#pragma unroll
+        for (int j = 0; j < C::CB; ++j)
+#pragma unroll
+            for (int u = 0; u < C::NU; ++u) r[s][j][u] = load(step * C::CB + j, u);
+    };
+    auto store = [&](int sb, int s) {
+#pragma unroll
+        for (int j = 0; j < C::CB; ++j)
+#pragma unroll
+            for (int u = 0; u < C::NU; ++u)
+                split_store4(r[s][j][u], dst + (sb * C::CB + j) * (3 * C::PLANE) + u * C::RP * SPROW, C::PLANE);
+    };
+#pragma unroll
+    for (int x = 0; x < C::WX; ++x)
+#pragma unroll
+        for (int y = 0; y < C::WY; ++y) acc[x][y] = f32x16{0};
+    const int ns = (nch + C::CB - 1) / C::CB;
+#pragma unroll
+    for (int s = 0; s < C::NS; ++s) fetch(s, s);
+    store(0, 0);
+    fetch(C::NS, 0);
+    __syncthreads();
+    // a step is multiplied from buffer step & 1; the next one waits in set (step + 1) mod NS
+    constexpr int U = C::NS % 2 ? 2 * C::NS : C::NS;
+    for (int c0 = 0; c0 < ns; c0 += U) {
+#pragma unroll
+        for (int i = 0; i < U; ++i) {
+            const int c = c0 + i;
+            if (c < ns) {   // uniform
+#pragma unroll
+                for (int j = 0; j < C::CB; ++j) {
+                    const int o = ((i & 1) * C::CB + j) * (3 * C::PLANE);
+                    split_mma<C::WX, C::WY>(fa + o, fb + o, C::PLANE, l, acc);
+                }
+                if (c + 1 < ns) {
+                    store((i & 1) ^ 1, (i + 1) % C::NS);
+                    fetch(c + 1 + C::NS, (i + 1) % C::NS);
+                }
+                __syncthreads();
+            }
+        }
+    }
 }
 
 }  // namespace bk

@@ -180,6 +180,23 @@ def test_poisoned_workspace_bitwise(m, n, k, identity_B):
                                                                ref_ad[1].view(np.uint32))
 
 
+def test_macro_tiles_bitwise(oracle_mod, monkeypatch):
+    """Every macro tile size of the node pushes gives the same bits (partial
+    macro tiles on both edges), so does a repeated solve; the widest against
+    the oracle's tie-forced replay."""
+    p = _problem(1000, 1060, seed=4100)
+    ref = None
+    for macro in (8, 4, 2):
+        log(f"case macro tile {macro} bitwise")
+        monkeypatch.setenv("BAKRON_MACRO", str(macro))
+        got = gpu_run(p, k=8)
+        if ref is None:
+            ref = got
+            check_against_oracle(p, *got, oracle_mod, label="macro8", method="recursive")
+        for a, b in zip(got, ref):
+            assert np.array_equal(a, b, equal_nan=a.dtype.kind == "f")
+
+
 @pytest.mark.parametrize("macro,k", [(4, 8), (4, 0), (2, 8)])
 def test_parity_forced_macro_tile(oracle_mod, macro, k):
     """BAKRON_MACRO=4 makes every node push use the 128 x 128 macro tiles
