@@ -7,7 +7,7 @@
 // columns.  Two levels of blocking (GPTQ's lazy batch updates):
 //   * ranges of GR column tiles (1024 columns).  Once a range is rounded, its
 //     errors are pushed into every later column of a working copy W' of W
-//     in one full-chip product on fp32 MFMA (k_gptq_push), so the bulk of
+//     in one full-chip product (k_gptq_push), so the bulk of
 //     the O(mn^2) work does not depend on how many rows there are;
 //   * inside a range, blocks of 32 columns (one factor tile), k_gptq:
 //     1. lazy feedback: W~[rows, blk] = W'[rows, blk] + E[rows, range start
@@ -17,15 +17,23 @@
 //        row, then add E[:, j] L^A[q, j] to the later columns q of the block.
 // The sums are the same elementary updates of Eq. (1), in another order.
 //
-// A k_gptq workgroup owns 16 rows and walks the blocks of one range.  In
-// step 1 each of its 4 waves multiplies a quarter of the source tiles with
-// v_mfma_f32_16x16x4f32 (A = the 16 error rows, B = the factor tile rows, so
-// D[i][j] = sum_k E[i][k] L^A[j][k]), with the operands of its next two
-// tiles in flight; the four partial sums meet in LDS.  In step 2 each wave
-// owns 4 rows, 16 lanes per row with the block columns c and c + 16 in
-// registers; the error of column j is broadcast along its 16 lanes with a
-// lane shuffle, so no barrier is needed inside the block.
+// A k_gptq workgroup owns 16 rows and walks the blocks of one range; the
+// range's errors stay in LDS.  In step 1 each of its 4 waves multiplies a
+// quarter of the source tiles with v_mfma_f32_16x16x4f32 (A = the 16 error rows,
+// B = the factor tile rows, so D[i][j] = sum_k E[i][k] L^A[j][k]), with the
+// factor tiles of the next two in flight; the four partial sums meet in LDS.
+// In step 2 each wave owns 4 rows, 16 lanes per row with the block columns c
+// and c + 16 in registers; the error of column j is broadcast along its 16
+// lanes with a DPP row broadcast, so no barrier is needed inside the block.
+// What bounds it: the chain of 32 dependent columns per block and the memory
+// latency between two blocks, so all that a block needs besides the errors is
+// read ahead of it.  512 x 1500 (47 blocks, one push): 334 us with a lane shuffle
+// through LDS per column, the errors re-read from memory and the block's inputs
+// read after step 1; 253 us now.
+#include <utility>
+
 #include "common.h"
+#include "split.h"
 
 namespace bk {
 
@@ -45,6 +53,7 @@ struct GptqArgs {
 };
 
 constexpr int GR = 32;   // column tiles per range (1024 columns; the default of run_gptq)
+constexpr int GR_MAX = 64;   // the most that a range may have (a debug setting)
 
 __device__ inline f32x4 ld4(const float* p) { return *reinterpret_cast<const f32x4*>(p); }
 
@@ -57,8 +66,18 @@ __device__ inline void mfma16_8(f32x4 a0, f32x4 a1, f32x4 b0, f32x4 b1, f32x4& a
 
 constexpr int GW = 4;   // waves per workgroup
 
-__global__ __launch_bounds__(64 * GW) void k_gptq(GptqArgs a) {
+// f(0), f(1), .. with the index as a constant
+template <class F, int... J>
+__device__ __forceinline__ void columns(F& f, std::integer_sequence<int, J...>) {
+    (f(std::integral_constant<int, J>{}), ...);
+}
+
+// RT: column tiles per range at most (the errors of the range stay in LDS)
+template <int RT>
+__global__ __launch_bounds__(64 * GW, 2) void k_gptq(GptqArgs a) {
+    constexpr int ESTR = RT * TS + 4;
     __shared__ float part[GW][16][33];   // per wave: partial 16 x 32 lazy products
+    __shared__ __attribute__((aligned(16))) float Es[16][ESTR];   // errors of the range
     const int tid = threadIdx.x;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63;
     const int64_t row0 = (int64_t)blockIdx.x * 16;
@@ -70,45 +89,53 @@ __global__ __launch_bounds__(64 * GW) void k_gptq(GptqArgs a) {
     const float qlo = a.q.qlo, qhi = a.q.qhi;
     const float nan = __builtin_nanf("");
 
+    // the factor tiles of the wave's next two sources; the first two of a block
+    // are read while the block before it is rounded
+    f32x4 f[2][4];
+    auto ldf = [&](const float* p, int q) {
+        f[q][0] = ld4(p);
+        f[q][1] = ld4(p + 4);
+        f[q][2] = ld4(p + 16 * TS);
+        f[q][3] = ld4(p + 16 * TS + 4);
+    };
     for (int b = a.b_begin; b < a.b_end; ++b) {
+        // the block's own inputs, in flight during step 1: base values, scales and
+        // L^A[col][blk] of the lane's two columns
+        const int64_t col0 = (int64_t)b * TS + c16, col1 = col0 + 16;
+        const bool in0 = row < a.m && col0 < a.n, in1 = row < a.m && col1 < a.n;
+        const float w0 = in0 ? a.Wb[row * a.ldWb + col0] : 0.0f;
+        const float w1 = in1 ? a.Wb[row * a.ldWb + col1] : 0.0f;
+        const float s0 = entry_scale(a.q, row, col0, a.m, a.n);
+        const float s1 = entry_scale(a.q, row, col1, a.m, a.n);
+        f32x4 u0[TS / 4], u1[TS / 4];
+        {
+            const float* d = a.LA + packed_tile_offset(b, b);
+#pragma unroll
+            for (int j = 0; j < TS / 4; ++j) {
+                u0[j] = ld4(d + c16 * TS + 4 * j);
+                u1[j] = ld4(d + (16 + c16) * TS + 4 * j);
+            }
+        }
         // 1. lazy feedback from the range's source tiles kt < b (a quarter per wave),
-        // two tiles in flight: set 0 holds tiles w, w + 2 GW, ..., set 1
-        // tiles w + GW, w + 3 GW, ...
+        // the factor tiles of two in flight: set 0 holds tiles w, w + 2 GW,
+        // ..., set 1 tiles w + GW, w + 3 GW, ...; the errors are in LDS
         f32x4 acc0 = {0.0f, 0.0f, 0.0f, 0.0f}, acc1 = {0.0f, 0.0f, 0.0f, 0.0f};
         {
-            const float* erow = a.E + (row0 + i16) * a.ldE + 8 * s;
             const float* lt = a.LA + packed_tile_offset(b, 0) + i16 * TS + 8 * s;
-            f32x4 e0[2], e1[2], l0[2], l1[2], m0[2], m1[2];
-            auto ld = [&](int kt, int q) {
-                e0[q] = ld4(erow + kt * TS);
-                e1[q] = ld4(erow + kt * TS + 4);
-                l0[q] = ld4(lt + kt * TILE_ELEMS);
-                l1[q] = ld4(lt + kt * TILE_ELEMS + 4);
-                m0[q] = ld4(lt + kt * TILE_ELEMS + 16 * TS);
-                m1[q] = ld4(lt + kt * TILE_ELEMS + 16 * TS + 4);
-            };
-            auto mul = [&](int q) {
-                mfma16_8(e0[q], e1[q], l0[q], l1[q], acc0);   // output columns 0..15 of the block
-                mfma16_8(e0[q], e1[q], m0[q], m1[q], acc1);   // output columns 16..31
+            auto mul = [&](int kt, int q) {
+                const float* e = &Es[i16][(kt - a.b_begin) * TS + 8 * s];
+                const f32x4 x0 = ld4(e), x1 = ld4(e + 4);
+                mfma16_8(x0, x1, f[q][0], f[q][1], acc0);   // output columns 0..15 of the block
+                mfma16_8(x0, x1, f[q][2], f[q][3], acc1);   // output columns 16..31
             };
             int kt = a.b_begin + w;
-            if (kt < b) ld(kt, 0);
-            if (kt + GW < b) ld(kt + GW, 1);
             for (; kt + GW < b; kt += 2 * GW) {
-                {
-                    const f32x4 x0 = e0[0], x1 = e1[0], y0 = l0[0], y1 = l1[0], z0 = m0[0], z1 = m1[0];
-                    if (kt + 2 * GW < b) ld(kt + 2 * GW, 0);
-                    mfma16_8(x0, x1, y0, y1, acc0);
-                    mfma16_8(x0, x1, z0, z1, acc1);
-                }
-                {
-                    const f32x4 x0 = e0[1], x1 = e1[1], y0 = l0[1], y1 = l1[1], z0 = m0[1], z1 = m1[1];
-                    if (kt + 3 * GW < b) ld(kt + 3 * GW, 1);
-                    mfma16_8(x0, x1, y0, y1, acc0);
-                    mfma16_8(x0, x1, z0, z1, acc1);
-                }
+                mul(kt, 0);
+                if (kt + 2 * GW < b) ldf(lt + (kt + 2 * GW) * TILE_ELEMS, 0);
+                mul(kt + GW, 1);
+                if (kt + 3 * GW < b) ldf(lt + (kt + 3 * GW) * TILE_ELEMS, 1);
             }
-            if (kt < b) mul(0);
+            if (kt < b) mul(kt, 0);
         }
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
@@ -118,52 +145,53 @@ __global__ __launch_bounds__(64 * GW) void k_gptq(GptqArgs a) {
         __syncthreads();
 
         // 2. the block's 32 columns in order, 16 lanes per row
-        const int64_t col0 = (int64_t)b * TS + c16, col1 = col0 + 16;
         float h0 = part[0][rr][c16], h1 = part[0][rr][16 + c16];
 #pragma unroll
         for (int v = 1; v < GW; ++v) {
             h0 += part[v][rr][c16];
             h1 += part[v][rr][16 + c16];
         }
-        if (row < a.m && col0 < a.n) h0 += a.Wb[row * a.ldWb + col0];
-        if (row < a.m && col1 < a.n) h1 += a.Wb[row * a.ldWb + col1];
-        const float s0 = entry_scale(a.q, row, col0, a.m, a.n);
-        const float s1 = entry_scale(a.q, row, col1, a.m, a.n);
+        if (in0) h0 += w0;
+        if (in1) h1 += w1;
         const float is0 = s0 > 0.0f ? 1.0f / s0 : 0.0f;   // zero scale: alphabet {0}
         const float is1 = s1 > 0.0f ? 1.0f / s1 : 0.0f;
-        // L^A[col][blk] of the lane's two columns, strictly below the diagonal
+        // strictly below the diagonal
         float c0[TS], c1[TS];
-        {
-            const float* d = a.LA + packed_tile_offset(b, b);
-#pragma unroll
-            for (int j = 0; j < TS; j += 4) {
-                const f32x4 u = ld4(d + c16 * TS + j), v = ld4(d + (16 + c16) * TS + j);
-#pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    c0[j + t] = (j + t < c16) ? u[t] : 0.0f;
-                    c1[j + t] = (j + t < 16 + c16) ? v[t] : 0.0f;
-                }
-            }
-        }
-        float e0 = 0.0f, e1 = 0.0f, x0 = 0.0f, x1 = 0.0f;
 #pragma unroll
         for (int j = 0; j < TS; ++j) {
-            const bool hi = j >= 16;                       // column j sits in slot 1
+            c0[j] = j < c16 ? u0[j >> 2][j & 3] : 0.0f;
+            c1[j] = j < 16 + c16 ? u1[j >> 2][j & 3] : 0.0f;
+        }
+        if (b + 1 < a.b_end) {
+            const float* lt = a.LA + packed_tile_offset(b + 1, 0) + i16 * TS + 8 * s;
+            const int kt = a.b_begin + w;
+            if (kt <= b) ldf(lt + kt * TILE_ELEMS, 0);
+            if (kt + GW <= b) ldf(lt + (kt + GW) * TILE_ELEMS, 1);
+        }
+        float e0 = 0.0f, e1 = 0.0f, x0 = 0.0f, x1 = 0.0f;
+        auto column = [&](auto C) {
+            constexpr int j = C.value;
+            constexpr bool hi = j >= 16;                   // column j sits in slot 1
             const float hv = hi ? h1 : h0, iv = hi ? is1 : is0, sv = hi ? s1 : s0;
             const float xv = hv * iv;
             const float cq = __builtin_amdgcn_fmed3f(rintf(xv), qlo, qhi);
             const float ev = fmaf(cq, sv, -hv);
-            // the owner of column j is lane (j & 15) of the row's 16 lanes
-            const float ej = __shfl(ev, (l & 48) | (j & 15), 64);
+            // the owner of column j is lane (j & 15) of the row's 16 lanes: DPP row
+            // broadcast (row_newbcast), one operation instead of a trip through LDS
+            const float ej = __int_as_float(
+                __builtin_amdgcn_update_dpp(0, __float_as_int(ev), 0x150 + (j & 15), 0xf, 0xf, true));
             if (c16 == (j & 15)) {
                 if (hi) { e1 = ev; x1 = xv; } else { e0 = ev; x0 = xv; }
             }
             h0 = fmaf(ej, c0[j], h0);
             h1 = fmaf(ej, c1[j], h1);
-        }
+        };
+        columns(column, std::make_integer_sequence<int, TS>{});
         // errors for the later blocks (every workspace row and column is
         // written, padding included: its errors are 0); outputs
-        a.E[row * a.ldE + col0] = e0;
+        Es[rr][(b - a.b_begin) * TS + c16] = e0;
+        Es[rr][(b - a.b_begin) * TS + 16 + c16] = e1;
+        a.E[row * a.ldE + col0] = e0;   // (for the push)
         a.E[row * a.ldE + col1] = e1;
         if (row < a.m) {
             if (col0 < a.n) {
@@ -186,13 +214,11 @@ __global__ __launch_bounds__(64 * GW) void k_gptq(GptqArgs a) {
 }
 
 // The push of a finished range: Wout[p][q] = Win[p][q] + sum_k E[p][k] L^A[q][k]
-// over the range's columns k, for every later column q >= qb.  One workgroup
-// per MT x MT block of 32 x 32 tiles of W', 4 waves in a 2 x 2 arrangement,
-// each MT/2 x MT/2 blocks of v_mfma_f32_32x32x2f32; the range's K in chunks
-// of one tile (32), staged through double-buffered LDS with 16-byte rows,
-// the chunks two ahead prefetched into registers while the current one is
-// multiplied (within a chunk lane half h supplies k = 16 h + s at step s).
-// The same pipeline as the two-sided node push, on row-major E and W'.
+// over the range's columns k, for every later column q >= qb, on the bf16
+// matrix cores with both operands split in three (split.h).  One workgroup per
+// MT x MT block of 32 x 32 tiles of W'.  Measured against fp32 MFMA with 128 x 128
+// blocks: the whole solve of 4096 x 14336 10.9 -> 9.0 ms, 8192 x 8192 7.0 -> 5.9; the
+// 64 x 64 blocks of small pushes take as long as before.
 struct PushArgs {
     int64_t m, m16, n;
     int nt;
@@ -207,88 +233,51 @@ struct PushArgs {
     int64_t qb;       // first column of the later ranges (a multiple of 32)
 };
 
-constexpr int PSTR = TS + 4;   // LDS row stride (floats): 16-byte rows
-
 template <int MT>
-__global__ __launch_bounds__(256, (MT == 4 ? 2 : 4)) void k_gptq_push(PushArgs a) {
-    constexpr int WB = MT / 2;
-    __shared__ __attribute__((aligned(16))) float As[2][MT * TS][PSTR];
-    __shared__ __attribute__((aligned(16))) float Bs[2][MT * TS][PSTR];
+__global__ __launch_bounds__(SplitShape<MT>::TH, 2) void k_gptq_push(PushArgs a) {
+    using C = SplitShape<MT>;
+    __shared__ __attribute__((aligned(16))) uint16_t S[C::LDS];
     const int tid = threadIdx.x;
-    const int wv = tid >> 6, l = tid & 63;
-    const int wm = wv >> 1, wn = wv & 1;
-    const int lr = l & 31, lk = l >> 5;
-    const int srow = tid >> 3, sk = (tid & 7) * 4;   // staging: one float4 of each tile
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63;
+    const int wm = wv / C::WN, wn = wv % C::WN;
     const int64_t p0 = (int64_t)blockIdx.y * (MT * TS), q0 = a.qb + (int64_t)blockIdx.x * (MT * TS);
-    const int Q0 = (int)(q0 / TS);
 
-    f32x4 ra[2][MT], rb[2][MT];
-    auto load = [&](int kt, int r) {
+    // the thread's rows of its operand (E, or the factor's rows: row r of tile
+    // row Q sits at packed_tile_offset(Q, kt) + 32 r); rows past the end are
+    // read from the first row (valid memory) and staged as zeros
+    const bool opb = wv >= C::TH / 128;
+    const int th = tid & (C::TH / 2 - 1), kq = 4 * (th & 3);
+    const float* base[C::NU];
+    bool in[C::NU];
 #pragma unroll
-        for (int t = 0; t < MT; ++t) {
-            const int64_t p = p0 + t * TS + srow;
-            const bool kin = kt < a.ke;
-            ra[r][t] = (kin && p < a.m16) ? *reinterpret_cast<const f32x4*>(a.E + p * a.ldE + (int64_t)kt * TS + sk)
-                                          : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-            rb[r][t] = (kin && Q0 + t < a.nt)
-                           ? *reinterpret_cast<const f32x4*>(a.LA + packed_tile_offset(Q0 + t, kt) + tid * 4)
-                           : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    for (int u = 0; u < C::NU; ++u) {
+        const int r = (th >> 2) + u * C::RP;
+        if (!opb) {
+            in[u] = p0 + r < a.m16;
+            base[u] = a.E + (in[u] ? p0 + r : 0) * a.ldE + (int64_t)a.kb * TS + kq;
+        } else {
+            const int64_t Q = q0 / TS + (r >> 5);
+            in[u] = Q < a.nt;
+            base[u] = a.LA + packed_tile_offset(in[u] ? Q : q0 / TS, a.kb) + (r & (TS - 1)) * TS + kq;
         }
-    };
-    auto store = [&](int s, int r) {
-#pragma unroll
-        for (int t = 0; t < MT; ++t) {
-            *reinterpret_cast<f32x4*>(&As[s][t * TS + srow][sk]) = ra[r][t];
-            *reinterpret_cast<f32x4*>(&Bs[s][t * TS + srow][sk]) = rb[r][t];
-        }
-    };
-    f32x16 acc[WB][WB];
-#pragma unroll
-    for (int x = 0; x < WB; ++x)
-#pragma unroll
-        for (int y = 0; y < WB; ++y) acc[x][y] = f32x16{0};
-    auto chunk = [&](int kt, int s, int r) {
-        load(kt + 2, r);   // past the range: zeros, nothing read
-        f32x4 fa[WB][4], fb[WB][4];
-#pragma unroll
-        for (int x = 0; x < WB; ++x)
-#pragma unroll
-            for (int v = 0; v < 4; ++v)
-                fa[x][v] = *reinterpret_cast<const f32x4*>(&As[s][(wm * WB + x) * TS + lr][lk * 16 + v * 4]);
-#pragma unroll
-        for (int y = 0; y < WB; ++y)
-#pragma unroll
-            for (int v = 0; v < 4; ++v)
-                fb[y][v] = *reinterpret_cast<const f32x4*>(&Bs[s][(wn * WB + y) * TS + lr][lk * 16 + v * 4]);
-#pragma unroll
-        for (int st = 0; st < 16; ++st) {
-#pragma unroll
-            for (int x = 0; x < WB; ++x)
-#pragma unroll
-                for (int y = 0; y < WB; ++y)
-                    acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[x][st >> 2][st & 3],
-                                                                    fb[y][st >> 2][st & 3], acc[x][y], 0, 0, 0);
-        }
-        if (kt + 1 < a.ke) store(s ^ 1, r ^ 1);
-        __syncthreads();
-    };
-    load(a.kb, 0);
-    load(a.kb + 1, 1);
-    store(0, 0);
-    __syncthreads();
-    for (int kt = a.kb; kt < a.ke; kt += 2) {
-        chunk(kt, 0, 0);
-        if (kt + 1 < a.ke) chunk(kt + 1, 1, 1);
     }
+    const int64_t stride = opb ? TILE_ELEMS : TS;
+    const int nch = 2 * (a.ke - a.kb);
+    f32x16 acc[C::WX][C::WY];
+    split_gemm<MT>(S, nch, tid, [&](int c, int u) {
+        const int k = c < nch ? c : nch - 1;   // past the range: not used
+        const f32x4 v = *reinterpret_cast<const f32x4*>(base[u] + (k >> 1) * stride + (k & 1) * 16);
+        return in[u] ? v : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    }, acc);
 #pragma unroll
-    for (int x = 0; x < WB; ++x)
+    for (int x = 0; x < C::WX; ++x)
 #pragma unroll
-        for (int y = 0; y < WB; ++y) {
-            const int64_t q = q0 + (wn * WB + y) * TS + lr;
+        for (int y = 0; y < C::WY; ++y) {
+            const int64_t q = q0 + (wn * C::WY + y) * TS + (l & 31);
             if (q >= a.n) continue;
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                const int64_t p = p0 + (wm * WB + x) * TS + (r >> 2) * 8 + lk * 4 + (r & 3);
+                const int64_t p = p0 + (wm * C::WX + x) * TS + (r >> 2) * 8 + (l >> 5) * 4 + (r & 3);
                 if (p < a.m) a.Wout[p * a.ldOut + q] = a.Win[p * a.ldIn + q] + acc[x][y][r];
             }
         }
@@ -325,7 +314,10 @@ hipError_t run_gptq(hipStream_t st, const float* W, int64_t m, int64_t n, const 
         a.b_end = b1;
         a.Wb = b0 == 0 ? W : Wt;
         a.ldWb = b0 == 0 ? n : ldE;
-        hipLaunchKernelGGL(k_gptq, dim3((unsigned)(m16 / 16)), dim3(64 * GW), 0, st, a);
+        if (R <= GR)
+            hipLaunchKernelGGL(k_gptq<GR>, dim3((unsigned)(m16 / 16)), dim3(64 * GW), 0, st, a);
+        else
+            hipLaunchKernelGGL(k_gptq<GR_MAX>, dim3((unsigned)(m16 / 16)), dim3(64 * GW), 0, st, a);
         if (b1 < nt) {
             PushArgs pa;
             pa.m = m;
@@ -342,15 +334,16 @@ hipError_t run_gptq(hipStream_t st, const float* W, int64_t m, int64_t n, const 
             pa.ke = b1;
             pa.qb = (int64_t)b1 * TS;
             pa.nt = nt;
-            // 128 x 128 blocks when they fill the chip twice over, else 64 x 64
-            const int64_t big = ((n - pa.qb + 127) / 128) * ((m + 127) / 128);
-            if (big >= 512) {
-                const dim3 grid((unsigned)((n - pa.qb + 127) / 128), (unsigned)((m + 127) / 128));
-                hipLaunchKernelGGL(k_gptq_push<4>, grid, dim3(256), 0, st, pa);
-            } else {
-                const dim3 grid((unsigned)((n - pa.qb + 63) / 64), (unsigned)((m + 63) / 64));
-                hipLaunchKernelGGL(k_gptq_push<2>, grid, dim3(256), 0, st, pa);
-            }
+            // the widest blocks that give every CU one (256 x 256) or two (128 x
+            // 128) workgroups, else 64 x 64
+            auto blocks = [&](int64_t e) { return dim3((unsigned)((n - pa.qb + e - 1) / e), (unsigned)((m + e - 1) / e)); };
+            const dim3 g8 = blocks(256), g4 = blocks(128), g2 = blocks(64);
+            if ((int64_t)g8.x * g8.y >= 256)
+                hipLaunchKernelGGL(k_gptq_push<8>, g8, dim3(SplitShape<8>::TH), 0, st, pa);
+            else if ((int64_t)g4.x * g4.y >= 256)
+                hipLaunchKernelGGL(k_gptq_push<4>, g4, dim3(SplitShape<4>::TH), 0, st, pa);
+            else
+                hipLaunchKernelGGL(k_gptq_push<2>, g2, dim3(SplitShape<2>::TH), 0, st, pa);
         }
     }
     return hipGetLastError();
