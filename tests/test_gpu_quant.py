@@ -107,6 +107,31 @@ def test_mse_scales_parity(oracle_mod, bits, alphabet, group):
         check_against_oracle(p, codes, V, pre, oracle_mod, label="mse-solve")
 
 
+@pytest.mark.parametrize("exp", [0, -123, -140, 110, 124])
+@pytest.mark.parametrize("alphabet", ["sym", "asym"])
+def test_mse_scales_boundaries(oracle_mod, exp, alphabet):
+    """Entries on and one ulp beside the rounding boundaries (k + 1/2) s, for
+    scales in the middle of fp32's range, subnormal ones and ones whose
+    reciprocal is subnormal: the same picks as the oracle's IEEE divisions."""
+    import torch
+    import paper_2608_06291_amd as pk
+    log(f"case mse boundaries exp={exp} {alphabet}")
+    bits = 8
+    k = np.arange(-128, 128, dtype=np.float64)
+    half = ((k + 0.5) * 2.0 ** -4).astype(np.float32)
+    rows = [np.concatenate([half, np.nextafter(half, np.float32(np.inf)),
+                            np.nextafter(half, np.float32(-np.inf)), [np.float32(t)]])
+            for t in (127 * 2.0 ** -4, 9.0, 11.3)]
+    W = np.ldexp(np.array(rows, np.float32), exp).astype(np.float32)
+    got = pk.mse_scales(torch.from_numpy(W).to("cuda:0"), bits, alphabet).cpu().numpy()
+    ref, err = oracle_mod.mse_scales(W, bits, alphabet)
+    for i in range(len(rows)):
+        if got[i] != ref[i]:   # another pick only where the fp64 sums agree
+            cand = oracle_mod.mse_scale_candidates(W, bits, alphabet)[i]
+            hit = np.flatnonzero(cand == got[i])
+            assert hit.size and abs(err[i][hit[0]] - err[i].min()) <= 1e-12 * err[i].min()
+
+
 @pytest.mark.parametrize("nheads,hb,n", [(4, 32, 80), (3, 48, 70), (8, 16, 33)])
 def test_block_diagonal_B_parity(oracle_mod, nheads, hb, n):
     """B = blockdiag of per-head Grams (App. D): parity with the oracle on the
