@@ -1,16 +1,28 @@
 // fp32 products on the bf16 matrix cores, at fp32 precision.
 //
-// Every fp32 operand x is split without loss into three bf16 numbers,
-//     x = h + m + l :  h = x truncated to 8 bits, m = x - h rounded to 8 bits,
-//     l = the rest (at most 8 bits, so exact),
+// Every fp32 operand x is split into three bf16 numbers (the three-way bf16
+// splitting of Henry, Tang and Heinecke, "Leveraging the bfloat16 Artificial
+// Intelligence Datatype For Higher-Precision Computations", ARITH 2019),
+//     x = h + m + l :  h = x rounded to 8 bits, m = x - h rounded to 8 bits,
+//     l = the rest (at most 7 bits, so exact),
 // and a product a b is the sum of the six partial products
 //     l_a h_b + h_a l_b + m_a m_b + m_a h_b + h_a m_b + h_a h_b ,
 // each exact in fp32 (8 x 8 bits) and added into the fp32 accumulator of
-// v_mfma_f32_32x32x16_bf16, small ones first.  What is left out, m l + l m + l l,
-// is below 2^-22 of |a b| (2^-26 on average, of either sign: m is rounded to
-// nearest), under the half ulp that any fp32 summation loses at every step.
-// Sixteen k's share one rounding per partial product, against two k's per
-// rounding of v_mfma_f32_32x32x2f32.
+// v_mfma_f32_32x32x16_bf16, small ones first.
+//
+// Precision (u = 2^-24, half an ulp).  What is left out, m l + l m + l l, is of
+// either sign and at most u |a b| (operands just above a power of two; rms 2^-26
+// to 2^-27.5).  With the matrix core's own rounding a single product is off by
+// up to 2.7 u |a b| (measured; one fp32 operation 1 u).  Sixteen k's share one
+// rounding per partial product, against two k's per rounding of
+// v_mfma_f32_32x32x2f32, so from 3 or 4 terms on a sum is nearer to its 64-bit
+// value than with fp32 MFMA: rms against sum |a b| over 1, 2, 4, 16, 2000 terms 0.57,
+// 0.47, 0.36, 0.21, 0.10 u here and 0.43, 0.44, 0.45, 0.48, 0.13 u there (normal
+// operands).  With h truncated instead of rounded, at the same cost, the part left
+// out is four times as large (single products up to 5.4 u).
+// Range: the split is exact for |x| >= 2^-110; below, l falls under bf16's
+// smallest number and x is kept to within 2^-133.  An operand that is not finite,
+// or above 2^128 - 2^119 (h rounds to infinity), makes the products it enters NaN.
 //
 // Why: the dense bf16 rate is 16 times the fp32 MFMA rate, six products leave
 // a factor 2.7 for the matrix cores (large products here reach 154 TFLOP/s in
@@ -37,11 +49,10 @@ struct SplitPair {
     uint32_t h, m, l;
 };
 __device__ inline SplitPair split_pair(float a, float b) {
-    const uint32_t ua = __float_as_uint(a), ub = __float_as_uint(b);
     SplitPair s;
-    s.h = __builtin_amdgcn_perm(ub, ua, 0x07060302u);   // the two high halves
-    const float ra = a - __uint_as_float(ua & 0xffff0000u);
-    const float rb = b - __uint_as_float(ub & 0xffff0000u);
+    s.h = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{a, b}, bf16x2));
+    const float ra = a - __uint_as_float(s.h << 16);
+    const float rb = b - __uint_as_float(s.h & 0xffff0000u);
     s.m = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{ra, rb}, bf16x2));
     const float ta = ra - __uint_as_float(s.m << 16);
     const float tb = rb - __uint_as_float(s.m & 0xffff0000u);
@@ -51,8 +62,9 @@ __device__ inline SplitPair split_pair(float a, float b) {
 
 // Splits four consecutive k's of one row and writes the three planes
 // (`plane` bf16 slots apart) at dst.  A non-finite entry has m = l = NaN, so
-// every product with it is NaN (in plain fp32 it is infinite or NaN); products
-// without it are not touched.
+// every product with it is NaN (in plain fp32 it is infinite or NaN), and finite
+// products that overflow can be NaN too (their parts overflow with both signs);
+// products without such an entry are not touched.
 __device__ inline void split_store4(f32x4 v, uint16_t* dst, int plane) {
     const SplitPair p = split_pair(v[0], v[1]), q = split_pair(v[2], v[3]);
     *reinterpret_cast<u32x2*>(dst) = u32x2{p.h, q.h};

@@ -103,6 +103,24 @@ def test_gram_and_quadform_block_edges(oracle_mod, N, d):
     assert not np.isfinite(Ci[d - 1]).any()
 
 
+@pytest.mark.parametrize("d", [96, 300])
+def test_gram_single_products(d):
+    """Sums with one term that is not zero (weight 1 on one of 64 samples), both
+    block sizes, mantissas just above 1 where the omitted parts of a split
+    product weigh most: at most 1 u left out, 2 u for the rounding of the last
+    partial product if the matrix core truncates, and 2^-7 of that for the small ones."""
+    import torch
+    import paper_2608_06291_amd as pk
+    log(f"case single products d={d}")
+    r = np.random.Generator(np.random.PCG64(np.random.SeedSequence([4020, d])))
+    X = (1 + 0.02 * r.random((64, d))).astype(np.float32)
+    w = np.zeros(64, np.float32)
+    w[5] = 1.0
+    C = pk.gram(_dev(X), _dev(w), 1.0).cpu().numpy().astype(np.float64)
+    ref = np.outer(X[5].astype(np.float64), X[5].astype(np.float64))
+    assert np.max(np.abs(C - ref) / ref) <= 3.1 * U32
+
+
 def test_gram_in_place_mask_empty_and_deterministic(oracle_mod):
     import torch
     import paper_2608_06291_amd as pk
