@@ -363,7 +363,8 @@ bakron_status bakron_solve_noalloc(const float *W, int64_t m, int64_t n, const b
  * Conventions of this group (in addition to those above):
  *   - sample matrices are N x d row-major fp32, one sample per row;
  *   - computed on the matrix cores at fp32 precision (three-way bf16 split of the
- *     operands, fp32 sums); a non-finite sample makes the entries it enters NaN; the
+ *     operands, fp32 sums; plain fp32 products for sums of at most 4 terms and for
+ *     results that are not finite, which are those of fp32 arithmetic); the
  *     summation order is fixed for a given device and shape, so repeated calls
  *     give bitwise the same result;
  *   - workspace protocol: with work == NULL the call stores the number of

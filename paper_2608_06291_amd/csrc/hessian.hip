@@ -26,6 +26,40 @@ constexpr int GB = 128;        // narrow block edge of the Gram and quadratic-fo
 constexpr int GBW = 256;       // wide block edge
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));   // rows at any 4-byte address
 
+// The same block in plain fp32 (v_mfma_f32_32x32x2f32), staged as [row][16 k's].
+// k_gram and k_quadform take it
+//   * for sums of at most PLAIN_TERMS terms, which the split makes less exact
+//     (a single product is off by up to 2.7 u, here 1 u; from 5 terms on the split
+//     is the more exact one: split.h);
+//   * in a second pass over a block in which a result of the split product is not
+//     finite, for those results only: an infinite operand, or finite products
+//     that overflow, give NaN in the split where fp32 has an infinity.
+// Neither needs speed, so LDS is single-buffered.
+constexpr int PLAIN_TERMS = 4;
+constexpr int PLROW = SPK + 4;   // floats per staged row: 16-byte rows, no bank conflicts
+
+// One chunk of a wave's WX x WY blocks of 32 x 32: lane half h takes k = 8 h + s at step s.
+template <int WX, int WY>
+__device__ inline void plain_mma(const float* a, const float* b, int l, f32x16 (&acc)[WX][WY]) {
+    const int off = (l & 31) * PLROW + (l >> 5) * 8;
+#pragma unroll
+    for (int v = 0; v < 2; ++v)
+#pragma unroll
+        for (int x = 0; x < WX; ++x) {
+            const f32x4 fa = *reinterpret_cast<const f32x4*>(a + x * 32 * PLROW + off + 4 * v);
+#pragma unroll
+            for (int y = 0; y < WY; ++y) {
+                const f32x4 fb = *reinterpret_cast<const f32x4*>(b + y * 32 * PLROW + off + 4 * v);
+#pragma unroll
+                for (int s = 0; s < 4; ++s)
+                    acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[s], fb[s], acc[x][y], 0, 0, 0);
+                asm volatile("" ::: "memory");   // few operands live at once
+            }
+        }
+}
+
+__device__ inline bool not_finite(float v) { return !(fabsf(v) <= 3.402823466e38f); }
+
 // ----------------------------------------------------------------------------
 // w[k] = sum_i c[i] * X[k][i]^2 (c null: c = 1).  One wave per sample row.
 template <bool VEC>
@@ -77,7 +111,7 @@ __global__ __launch_bounds__(256) void k_diag(const float* __restrict__ src, int
 // bf16 matrix cores at the clock they hold (the wide block needs 62% of the
 // LDS and a quarter of the VALU cycles of its MFMA time).  Measured, 524288
 // samples: 4096 features 79.8 -> 48.6 ms (110 -> 181 TFLOP/s) against the
-// fp32 MFMA kernel before it, with a relative error against 64 bits of 5e-7
+// same product on fp32 MFMA, with a relative error against 64 bits of 5e-7
 // instead of 3.8e-6; 400 features 1.58 -> 0.99 ms; rows that are not 16-byte
 // aligned (3001 features, 100000 samples) 11.6 -> 5.6 ms, as they were read
 // one float at a time.
@@ -139,13 +173,15 @@ __device__ inline int gram_work_of(int v, int total) {
     return (v % GXCD) * per + v / GXCD;
 }
 
-template <int GT, int WX, int WY>
+template <int GT, int WX, int WY, bool PLAIN>
 __global__ __launch_bounds__(64 * (GT / (32 * WX)) * (GT / (32 * WY)), 2) void k_gram(GramArgs a) {
     constexpr int WN = GT / (32 * WY);                   // waves along the columns
     constexpr int TH = 64 * (GT / (32 * WX)) * WN;
     static_assert(TH == 2 * GT, "one staging thread per 4 features x 4 samples of both operands");
     constexpr int PLANE = 2 * GT * SPROW;                // rows 0 .. GT - 1: A, GT .. 2 GT - 1: B
     __shared__ __attribute__((aligned(16))) uint16_t S[2][3 * PLANE];
+    static_assert(2 * GT * PLROW * 4 <= (int)sizeof(S), "fp32 staging");
+    __shared__ int redo;
     const int wk = gram_work_of((int)blockIdx.x, a.nblk * a.slices);
     if (wk >= a.nblk * a.slices) return;   // padding of the last XCD's range
     const int slice = wk / a.nblk;
@@ -194,7 +230,7 @@ __global__ __launch_bounds__(64 * (GT / (32 * WX)) * (GT / (32 * WY)), 2) void k
             }
         }
     };
-    auto store = [&](int sb) {
+    auto weigh = [&]() {
         if (!full || kbase + SPK > k_hi) {   // uniform: padding features or samples
 #pragma unroll
             for (int u = 0; u < 4; ++u)
@@ -210,6 +246,9 @@ __global__ __launch_bounds__(64 * (GT / (32 * WX)) * (GT / (32 * WY)), 2) void k
                 for (int v = 0; v < 4; ++v) r[u][v] *= x;
             }
         }
+    };
+    auto store = [&](int sb) {
+        weigh();
 #pragma unroll
         for (int v = 0; v < 4; ++v)
             split_store4(f32x4{r[0][v], r[1][v], r[2][v], r[3][v]},
@@ -220,30 +259,70 @@ __global__ __launch_bounds__(64 * (GT / (32 * WX)) * (GT / (32 * WY)), 2) void k
     for (int x = 0; x < WX; ++x)
 #pragma unroll
         for (int y = 0; y < WY; ++y) acc[x][y] = f32x16{0};
-    if (nch > 0) {
-        load(k_lo);
-        store(0);
+    // acc[x][y][q] is entry (row (WX wm + x) * 32 + (q >> 2) * 8 + (l >> 5) * 4 + (q & 3),
+    // column (WY wn + y) * 32 + (l & 31)) of the block
+    float* const P = a.part + ((int64_t)slice * a.nblk + blk) * (GT * GT) +
+                     (WX * wm * TS + (l >> 5) * 4) * GT + WY * wn * TS + (l & 31);
+    if (tid == 0) redo = PLAIN;
+    if constexpr (!PLAIN) {
+        if (nch > 0) {
+            load(k_lo);
+            store(0);
+        }
+        __syncthreads();
+        for (int c = 0; c < nch; ++c) {
+            const int sb = c & 1;
+            const bool more = c + 1 < nch;
+            if (more) load(k_lo + (int64_t)(c + 1) * SPK);
+            split_mma<WX, WY>(&S[sb][wm * WX * 32 * SPROW], &S[sb][(GT + wn * WY * 32) * SPROW], PLANE, l, acc);
+            if (more) store(sb ^ 1);
+            __syncthreads();
+        }
+        float z = 0.0f;   // stays 0 over finite entries
+#pragma unroll
+        for (int x = 0; x < WX; ++x)
+#pragma unroll
+            for (int y = 0; y < WY; ++y)
+#pragma unroll
+                for (int q = 0; q < 16; ++q) z = fmaf(acc[x][y][q], 0.0f, z);
+        if (z != 0.0f) redo = 1;   // (NaN; the same value from every lane)
     }
-    __syncthreads();
+    __syncthreads();   // (before the stores, which it would wait for)
+    if constexpr (!PLAIN) {
+#pragma unroll
+        for (int x = 0; x < WX; ++x)
+#pragma unroll
+            for (int y = 0; y < WY; ++y)
+#pragma unroll
+                for (int q = 0; q < 16; ++q) P[(x * TS + (q >> 2) * 8 + (q & 3)) * GT + y * TS] = acc[x][y][q];
+    }
+    if (!redo) return;   // uniform
+    float* const F = reinterpret_cast<float*>(&S[0][0]);   // rows 0 .. GT - 1: A, GT .. 2 GT - 1: B
+#pragma unroll
+    for (int x = 0; x < WX; ++x)
+#pragma unroll
+        for (int y = 0; y < WY; ++y) acc[x][y] = f32x16{0};
     for (int c = 0; c < nch; ++c) {
-        const int sb = c & 1;
-        const bool more = c + 1 < nch;
-        if (more) load(k_lo + (int64_t)(c + 1) * SPK);
-        split_mma<WX, WY>(&S[sb][wm * WX * 32 * SPROW], &S[sb][(GT + wn * WY * 32) * SPROW], PLANE, l, acc);
-        if (more) store(sb ^ 1);
+        load(k_lo + (int64_t)c * SPK);
+        weigh();
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            *reinterpret_cast<f32x4*>(F + (op * GT + fi + v) * PLROW + kq) = f32x4{r[0][v], r[1][v], r[2][v], r[3][v]};
+        __syncthreads();
+        plain_mma<WX, WY>(F + wm * WX * 32 * PLROW, F + (GT + wn * WY * 32) * PLROW, l, acc);
         __syncthreads();
     }
-    // acc[x][y][r] is entry (row (WX wm + x) * 32 + (r >> 2) * 8 + (l >> 5) * 4 + (r & 3),
-    // column (WY wn + y) * 32 + (l & 31)) of the block
-    float* P = a.part + ((int64_t)slice * a.nblk + blk) * (GT * GT);
+    int again = 0;   // opaque: the addresses of the first pass are not kept over this one
+    asm volatile("" : "+v"(again));
 #pragma unroll
     for (int x = 0; x < WX; ++x)
 #pragma unroll
         for (int y = 0; y < WY; ++y)
 #pragma unroll
             for (int q = 0; q < 16; ++q) {
-                const int row = (WX * wm + x) * TS + (q >> 2) * 8 + (l >> 5) * 4 + (q & 3);
-                P[row * GT + (WY * wn + y) * TS + (l & 31)] = acc[x][y][q];
+                float* const e = &P[again + (x * TS + (q >> 2) * 8 + (q & 3)) * GT + y * TS];
+                if (PLAIN || not_finite(*e)) *e = acc[x][y][q];
+                asm volatile("" ::: "memory");   // one entry at a time
             }
 }
 
@@ -361,10 +440,10 @@ static hipError_t run_gram(hipStream_t st, const GramGeom& g, const float* X, in
     const int64_t total = (int64_t)g.nblk * g.slices;
     const dim3 grid((unsigned)(((total + GXCD - 1) / GXCD) * GXCD));
     const unsigned subs = (unsigned)(g.nblk * (g.gt / TS) * (g.gt / TS));
-    if (g.gt == GBW)
-        hipLaunchKernelGGL((k_gram<GBW, 4, 2>), grid, dim3(2 * GBW), 0, st, a);
+    if (N <= PLAIN_TERMS)
+        hipLaunchKernelGGL((g.gt == GBW ? k_gram<GBW, 4, 2, true> : k_gram<GB, 2, 2, true>), grid, dim3(2 * g.gt), 0, st, a);
     else
-        hipLaunchKernelGGL((k_gram<GB, 2, 2>), grid, dim3(2 * GB), 0, st, a);
+        hipLaunchKernelGGL((g.gt == GBW ? k_gram<GBW, 4, 2, false> : k_gram<GB, 2, 2, false>), grid, dim3(2 * g.gt), 0, st, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (g.gt == GBW)
@@ -393,14 +472,16 @@ struct QuadArgs {
     float* part;   // [nJ][N]
 };
 
-template <int GT, int WX, int WY>
+template <int GT, int WX, int WY, bool PLAIN>
 __global__ __launch_bounds__(64 * (GT / (32 * WX)) * (GT / (32 * WY)), 2) void k_quadform(QuadArgs a) {
     constexpr int WN = GT / (32 * WY);
     constexpr int TH = 64 * (GT / (32 * WX)) * WN;
     static_assert(TH == 2 * GT, "one staging thread per 4 rows x 4 inner entries of both operands");
     constexpr int PLANE = 2 * GT * SPROW;
     __shared__ __attribute__((aligned(16))) uint16_t S[2][3 * PLANE];
+    static_assert(2 * GT * PLROW * 4 <= (int)sizeof(S), "fp32 staging");
     __shared__ float red[WN][GT];
+    __shared__ int redo;
     const int J = (int)(blockIdx.x % (unsigned)a.nJ);
     const int64_t R = blockIdx.x / (unsigned)a.nJ;
     const int64_t k0 = R * GT, j0 = (int64_t)J * GT;
@@ -445,46 +526,80 @@ __global__ __launch_bounds__(64 * (GT / (32 * WX)) * (GT / (32 * WY)), 2) void k
 #pragma unroll
         for (int y = 0; y < WY; ++y) acc[x][y] = f32x16{0};
     const int nch = (int)((d + SPK - 1) / SPK);
-    load(0);
-    store(0);
-    __syncthreads();
-    for (int c = 0; c < nch; ++c) {
-        const int sb = c & 1;
-        const bool more = c + 1 < nch;
-        if (more) load((int64_t)(c + 1) * SPK);
-        split_mma<WX, WY>(&S[sb][wm * WX * 32 * SPROW], &S[sb][(GT + wn * WY * 32) * SPROW], PLANE, l, acc);
-        if (more) store(sb ^ 1);
+    if (tid == 0) redo = PLAIN;
+    if constexpr (!PLAIN) {
+        load(0);
+        store(0);
         __syncthreads();
+        for (int c = 0; c < nch; ++c) {
+            const int sb = c & 1;
+            const bool more = c + 1 < nch;
+            if (more) load((int64_t)(c + 1) * SPK);
+            split_mma<WX, WY>(&S[sb][wm * WX * 32 * SPROW], &S[sb][(GT + wn * WY * 32) * SPROW], PLANE, l, acc);
+            if (more) store(sb ^ 1);
+            __syncthreads();
+        }
     }
     // acc[x][y][q] = Y(row (WX wm + x) * 32 + (q >> 2) * 8 + (l >> 5) * 4 + (q & 3),
     //                  column (WY wn + y) * 32 + (l & 31)); row sums of Y (.) X over
     // the wave's columns, then over the lanes of a row, then over the waves that
     // share the rows
-    const int lr = l & 31;
+    auto row_sum = [&](int l) -> float {   // of row tid, for tid < GT
+        const int lr = l & 31;
 #pragma unroll
-    for (int x = 0; x < WX; ++x)
+        for (int x = 0; x < WX; ++x)
 #pragma unroll
-        for (int q = 0; q < 16; ++q) {
-            const int row = (WX * wm + x) * TS + (q >> 2) * 8 + (l >> 5) * 4 + (q & 3);
-            const int64_t k = k0 + row;
-            float v = 0.0f;
+            for (int q = 0; q < 16; ++q) {
+                const int row = (WX * wm + x) * TS + (q >> 2) * 8 + (l >> 5) * 4 + (q & 3);
+                const int64_t k = k0 + row;
+                float v = 0.0f;
 #pragma unroll
-            for (int y = 0; y < WY; ++y) {
-                const int64_t j = j0 + (WY * wn + y) * TS + lr;
-                const float xv = (k < a.N && j < d) ? a.X[k * d + j] : 0.0f;
-                v = fmaf(acc[x][y][q], xv, v);
+                for (int y = 0; y < WY; ++y) {
+                    const int64_t j = j0 + (WY * wn + y) * TS + lr;
+                    const bool at = k < a.N && j < d;   // (a padding column of an infinite row holds NaN)
+                    v = fmaf(at ? acc[x][y][q] : 0.0f, at ? a.X[k * d + j] : 0.0f, v);
+                }
+#pragma unroll
+                for (int off = 16; off >= 1; off >>= 1) v += __shfl_xor(v, off, 32);
+                if (lr == 0) red[wn][row] = v;
             }
+        __syncthreads();
+        float v = 0.0f;
+        if (tid < GT) {
+            v = red[0][tid];
 #pragma unroll
-            for (int off = 16; off >= 1; off >>= 1) v += __shfl_xor(v, off, 32);
-            if (lr == 0) red[wn][row] = v;
+            for (int i = 1; i < WN; ++i) v += red[i][tid];
         }
-    __syncthreads();
-    if (tid < GT && k0 + tid < a.N) {
-        float v = red[0][tid];
-#pragma unroll
-        for (int i = 1; i < WN; ++i) v += red[i][tid];
-        a.part[(int64_t)J * a.N + k0 + tid] = v;
+        return v;
+    };
+    float v = 0.0f;
+    if constexpr (!PLAIN) {
+        v = row_sum(l);
+        if (tid < GT && not_finite(v)) redo = 1;   // (the same value from every lane)
     }
+    __syncthreads();
+    if (redo) {   // uniform
+        float* const F = reinterpret_cast<float*>(&S[0][0]);   // rows 0 .. GT - 1: X, GT .. 2 GT - 1: M
+#pragma unroll
+        for (int x = 0; x < WX; ++x)
+#pragma unroll
+            for (int y = 0; y < WY; ++y) acc[x][y] = f32x16{0};
+        for (int c = 0; c < nch; ++c) {
+            load((int64_t)c * SPK);
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                *reinterpret_cast<f32x4*>(F + (op * GT + row0 + u * (GT / 4)) * PLROW + kq) =
+                    in[u] ? r[u] : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+            __syncthreads();
+            plain_mma<WX, WY>(F + wm * WX * 32 * PLROW, F + (GT + wn * WY * 32) * PLROW, l, acc);
+            __syncthreads();
+        }
+        int l2 = l;   // opaque: the addresses of the first pass are not kept over this one
+        asm volatile("" : "+v"(l2));
+        const float p = row_sum(l2);
+        if (PLAIN || not_finite(v)) v = p;
+    }
+    if (tid < GT && k0 + tid < a.N) a.part[(int64_t)J * a.N + k0 + tid] = v;
 }
 
 __global__ __launch_bounds__(256) void k_quadform_reduce(const float* __restrict__ part, int nJ,
@@ -523,10 +638,12 @@ static hipError_t run_quadform(hipStream_t st, const float* X, int64_t N, int64_
     const int nJ = (int)std::max<int64_t>(1, (d + gt - 1) / gt);
     QuadArgs a{X, N, d, M, nJ, part};
     const dim3 grid((unsigned)(((N + gt - 1) / gt) * nJ));
-    if (wide)
-        hipLaunchKernelGGL((k_quadform<GBW, 4, 2>), grid, dim3(2 * GBW), 0, st, a);
+    if (d <= PLAIN_TERMS)   // (never wide)
+        hipLaunchKernelGGL((k_quadform<GB, 2, 2, true>), grid, dim3(2 * GB), 0, st, a);
+    else if (wide)
+        hipLaunchKernelGGL((k_quadform<GBW, 4, 2, false>), grid, dim3(2 * GBW), 0, st, a);
     else
-        hipLaunchKernelGGL((k_quadform<GB, 2, 2>), grid, dim3(2 * GB), 0, st, a);
+        hipLaunchKernelGGL((k_quadform<GB, 2, 2, false>), grid, dim3(2 * GB), 0, st, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_quadform_reduce, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, st, part,

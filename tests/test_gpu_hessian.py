@@ -121,6 +121,78 @@ def test_gram_single_products(d):
     assert np.max(np.abs(C - ref) / ref) <= 3.1 * U32
 
 
+@pytest.mark.parametrize("N", [1, 2, 3, 4, 5, 17])
+def test_short_sums(N):
+    """Sums of few terms (plain fp32 up to 4, split products from 5 on) stay
+    within the bound of fp32 summation, one rounding per term: N u sum |x_ki x_kj|,
+    and for a quadratic form of N inner entries N u per Y_kj and N + 1 more for
+    its sum over j (2 % on top for second-order terms)."""
+    import torch
+    import paper_2608_06291_amd as pk
+    log(f"case short sums N={N}")
+    r = np.random.Generator(np.random.PCG64(np.random.SeedSequence([4021, N])))
+    for narrow in (True, False):
+        def draw(*shape):
+            return (1 + 0.02 * r.random(shape) if narrow else r.standard_normal(shape)).astype(np.float32)
+        X = draw(N, 300)
+        C = pk.gram(_dev(X)).cpu().numpy().astype(np.float64)
+        X64 = X.astype(np.float64)
+        iu = np.triu_indices(300)
+        err = np.abs(C - X64.T @ X64)[iu] / (np.abs(X64).T @ np.abs(X64))[iu]
+        assert np.max(err) <= 1.02 * N * U32
+        Y, M = draw(3000, N), draw(N, N)
+        M = (np.triu(M) + np.triu(M, 1).T).astype(np.float32)
+        q = pk.quadform_weights(_dev(Y), _dev(M)).cpu().numpy().astype(np.float64)
+        Y64, M64 = Y.astype(np.float64), M.astype(np.float64)
+        bound = (2 * N + 1) * U32 * np.sum((np.abs(Y64) @ np.abs(M64)) * np.abs(Y64), axis=1)
+        assert np.all(np.abs(q - np.sum((Y64 @ M64) * Y64, axis=1)) <= 1.02 * bound)
+
+
+@pytest.mark.parametrize("N,d", [(100, 300), (9000, 515)])
+def test_gram_and_quadform_infinities(N, d):
+    """Infinite entries and products that overflow give what fp32 arithmetic gives
+    (infinite where the sum is, NaN for opposite infinities), and the entries
+    without them keep their bits; both block edges."""
+    import torch
+    import paper_2608_06291_amd as pk
+    log(f"case infinities N={N} d={d}")
+    r = np.random.Generator(np.random.PCG64(np.random.SeedSequence([4022, N])))
+    X = r.standard_normal((N, d)).astype(np.float32)
+    C0 = pk.gram(_dev(X)).cpu().numpy()
+    bad = {7: [(N // 2, np.inf)], 200: [(20, -np.inf)], 280: [(3, np.inf), (40, np.inf)]}
+    Xb = X.copy()
+    for j, e in bad.items():
+        for k, v in e:
+            Xb[k, j] = v
+    C = pk.gram(_dev(Xb)).cpu().numpy()
+    keep = np.ones((d, d), bool)
+    with np.errstate(invalid="ignore"):
+        for j in bad:
+            keep[j] = keep[:, j] = False
+            ref = np.sum(Xb.astype(np.float64) * Xb[:, j:j + 1].astype(np.float64), axis=0)
+            assert np.array_equal(C[j], ref.astype(np.float32), equal_nan=True) and not np.isfinite(ref).any()
+    assert np.array_equal(C[keep], C0[keep])
+    log("case overflow")
+    P = np.abs(X[:, :70]) + np.float32(0.1)
+    C = pk.gram(_dev(P * np.float32(1e25))).cpu().numpy()
+    assert np.all(C == np.inf)
+    big = np.zeros((8, 2), np.float32)
+    big[0] = [3.4e38, 0.5]   # the upper part of a split of 3.4e38 is infinite
+    C = pk.gram(_dev(big)).cpu().numpy()
+    assert C[0, 1] == np.float32(1.7e38) and C[1, 1] == 0.25 and C[0, 0] == np.inf
+    log("case quadratic form")
+    M = (P[:70, :70] + P[:70, :70].T).astype(np.float32)
+    w0 = pk.quadform_weights(_dev(P), _dev(M)).cpu().numpy()
+    Pb = P.copy()
+    Pb[3, 5] = np.inf
+    Pb[60, 69] = 3e38   # finite; its form overflows
+    w = pk.quadform_weights(_dev(Pb), _dev(M)).cpu().numpy()
+    assert w[3] == np.inf and w[60] == np.inf
+    keep = np.ones(N, bool)
+    keep[[3, 60]] = False
+    assert np.isfinite(w0).all() and np.array_equal(w[keep], w0[keep])
+
+
 def test_gram_in_place_mask_empty_and_deterministic(oracle_mod):
     import torch
     import paper_2608_06291_amd as pk
