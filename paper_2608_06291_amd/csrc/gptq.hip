@@ -17,8 +17,9 @@
 //        row, then add E[:, j] L^A[q, j] to the later columns q of the block.
 // The sums are the same elementary updates of Eq. (1), in another order.
 //
-// A k_gptq workgroup owns 16 rows and walks the blocks of one range; the
-// range's errors stay in LDS.  In step 1 each of its 4 waves multiplies a
+// A k_gptq workgroup owns 16 rows and walks the blocks of one range; the errors
+// of the last RT blocks stay in LDS, older ones of the range (if RT is less than
+// its length) are read back from memory.  In step 1 each of its 4 waves multiplies a
 // quarter of the source tiles with v_mfma_f32_16x16x4f32 (A = the 16 error rows,
 // B = the factor tile rows, so D[i][j] = sum_k E[i][k] L^A[j][k]), with the
 // factor tiles of the next two in flight; the four partial sums meet in LDS.
@@ -53,7 +54,6 @@ struct GptqArgs {
 };
 
 constexpr int GR = 32;   // column tiles per range (1024 columns; the default of run_gptq)
-constexpr int GR_MAX = 64;   // the most that a range may have (a debug setting)
 
 __device__ inline f32x4 ld4(const float* p) { return *reinterpret_cast<const f32x4*>(p); }
 
@@ -72,12 +72,14 @@ __device__ __forceinline__ void columns(F& f, std::integer_sequence<int, J...>) 
     (f(std::integral_constant<int, J>{}), ...);
 }
 
-// RT: column tiles per range at most (the errors of the range stay in LDS)
-template <int RT>
-__global__ __launch_bounds__(64 * GW, 2) void k_gptq(GptqArgs a) {
+// RT: the last RT column tiles of errors are kept in LDS (a ring); OLD: the range
+// may be longer, then the errors of the older tiles come from memory.  WG:
+// workgroups per CU.
+template <int RT, bool OLD, int WG>
+__global__ __launch_bounds__(64 * GW, WG) void k_gptq(GptqArgs a) {
     constexpr int ESTR = RT * TS + 4;
     __shared__ float part[GW][16][33];   // per wave: partial 16 x 32 lazy products
-    __shared__ __attribute__((aligned(16))) float Es[16][ESTR];   // errors of the range
+    __shared__ __attribute__((aligned(16))) float Es[16][ESTR];   // errors of the last RT tiles
     const int tid = threadIdx.x;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6), l = tid & 63;
     const int64_t row0 = (int64_t)blockIdx.x * 16;
@@ -91,12 +93,20 @@ __global__ __launch_bounds__(64 * GW, 2) void k_gptq(GptqArgs a) {
 
     // the factor tiles of the wave's next two sources; the first two of a block
     // are read while the block before it is rounded
-    f32x4 f[2][4];
-    auto ldf = [&](const float* p, int q) {
+    // (block bn, source tile kt; an old tile's errors were written RT blocks ago)
+    f32x4 f[2][4], eo[2][2];
+    const float* const lrow = a.LA + i16 * TS + 8 * s;
+    const float* const erow = a.E + (row0 + i16) * a.ldE + 8 * s;
+    auto ldf = [&](int bn, int kt, int q) {
+        const float* p = lrow + packed_tile_offset(bn, kt);
         f[q][0] = ld4(p);
         f[q][1] = ld4(p + 4);
         f[q][2] = ld4(p + 16 * TS);
         f[q][3] = ld4(p + 16 * TS + 4);
+        if (OLD && kt < bn - RT) {   // uniform
+            eo[q][0] = ld4(erow + kt * TS);
+            eo[q][1] = ld4(erow + kt * TS + 4);
+        }
     };
     for (int b = a.b_begin; b < a.b_end; ++b) {
         // the block's own inputs, in flight during step 1: base values, scales and
@@ -121,19 +131,22 @@ __global__ __launch_bounds__(64 * GW, 2) void k_gptq(GptqArgs a) {
         // ..., set 1 tiles w + GW, w + 3 GW, ...; the errors are in LDS
         f32x4 acc0 = {0.0f, 0.0f, 0.0f, 0.0f}, acc1 = {0.0f, 0.0f, 0.0f, 0.0f};
         {
-            const float* lt = a.LA + packed_tile_offset(b, 0) + i16 * TS + 8 * s;
             auto mul = [&](int kt, int q) {
-                const float* e = &Es[i16][(kt - a.b_begin) * TS + 8 * s];
-                const f32x4 x0 = ld4(e), x1 = ld4(e + 4);
+                f32x4 x0 = eo[q][0], x1 = eo[q][1];
+                if (!OLD || kt >= b - RT) {   // uniform
+                    const float* e = &Es[i16][(OLD ? (kt - a.b_begin) % RT : kt - a.b_begin) * TS + 8 * s];
+                    x0 = ld4(e);
+                    x1 = ld4(e + 4);
+                }
                 mfma16_8(x0, x1, f[q][0], f[q][1], acc0);   // output columns 0..15 of the block
                 mfma16_8(x0, x1, f[q][2], f[q][3], acc1);   // output columns 16..31
             };
             int kt = a.b_begin + w;
             for (; kt + GW < b; kt += 2 * GW) {
                 mul(kt, 0);
-                if (kt + 2 * GW < b) ldf(lt + (kt + 2 * GW) * TILE_ELEMS, 0);
+                if (kt + 2 * GW < b) ldf(b, kt + 2 * GW, 0);
                 mul(kt + GW, 1);
-                if (kt + 3 * GW < b) ldf(lt + (kt + 3 * GW) * TILE_ELEMS, 1);
+                if (kt + 3 * GW < b) ldf(b, kt + 3 * GW, 1);
             }
             if (kt < b) mul(kt, 0);
         }
@@ -163,10 +176,9 @@ __global__ __launch_bounds__(64 * GW, 2) void k_gptq(GptqArgs a) {
             c1[j] = j < 16 + c16 ? u1[j >> 2][j & 3] : 0.0f;
         }
         if (b + 1 < a.b_end) {
-            const float* lt = a.LA + packed_tile_offset(b + 1, 0) + i16 * TS + 8 * s;
             const int kt = a.b_begin + w;
-            if (kt <= b) ldf(lt + kt * TILE_ELEMS, 0);
-            if (kt + GW <= b) ldf(lt + (kt + GW) * TILE_ELEMS, 1);
+            if (kt <= b) ldf(b + 1, kt, 0);
+            if (kt + GW <= b) ldf(b + 1, kt + GW, 1);
         }
         float e0 = 0.0f, e1 = 0.0f, x0 = 0.0f, x1 = 0.0f;
         auto column = [&](auto C) {
@@ -189,9 +201,10 @@ __global__ __launch_bounds__(64 * GW, 2) void k_gptq(GptqArgs a) {
         columns(column, std::make_integer_sequence<int, TS>{});
         // errors for the later blocks (every workspace row and column is
         // written, padding included: its errors are 0); outputs
-        Es[rr][(b - a.b_begin) * TS + c16] = e0;
-        Es[rr][(b - a.b_begin) * TS + 16 + c16] = e1;
-        a.E[row * a.ldE + col0] = e0;   // (for the push)
+        const int es = (OLD ? (b - a.b_begin) % RT : b - a.b_begin) * TS;
+        Es[rr][es + c16] = e0;
+        Es[rr][es + 16 + c16] = e1;
+        a.E[row * a.ldE + col0] = e0;   // (for the push and for later blocks)
         a.E[row * a.ldE + col1] = e1;
         if (row < a.m) {
             if (col0 < a.n) {
@@ -297,6 +310,12 @@ hipError_t run_gptq(hipStream_t st, const float* W, int64_t m, int64_t n, const 
     const int nt = (int)((n + TS - 1) / TS);
     const int64_t ldE = (int64_t)nt * TS, m16 = (m + 15) / 16 * 16;
     float* Wt = E + m16 * ldE;
+    // All errors of the range in LDS: two workgroups fit a CU, 512 the chip.  The last
+    // half of them: three, 768.  The first is quicker while both take as many rounds of
+    // the chip, and where it takes two full rounds against one and a third (us at n =
+    // 1024, errors in LDS / in part from memory: 8192 rows 231 / 240, 12288 rows 451 / 331,
+    // 16384 rows 458 / 475, 20000 rows 675 / 568, 57344 rows 1657 / 1563).  Same bits.
+    const int64_t wg = m16 / 16;
     GptqArgs a;
     a.m = m;
     a.n = n;
@@ -314,10 +333,11 @@ hipError_t run_gptq(hipStream_t st, const float* W, int64_t m, int64_t n, const 
         a.b_end = b1;
         a.Wb = b0 == 0 ? W : Wt;
         a.ldWb = b0 == 0 ? n : ldE;
-        if (R <= GR)
-            hipLaunchKernelGGL(k_gptq<GR>, dim3((unsigned)(m16 / 16)), dim3(64 * GW), 0, st, a);
+        const dim3 rows((unsigned)wg);
+        if (R <= GR && (wg <= 512 || (wg > 768 && wg <= 1024)))
+            hipLaunchKernelGGL((k_gptq<GR, false, 2>), rows, dim3(64 * GW), 0, st, a);
         else
-            hipLaunchKernelGGL(k_gptq<GR_MAX>, dim3((unsigned)(m16 / 16)), dim3(64 * GW), 0, st, a);
+            hipLaunchKernelGGL((k_gptq<GR / 2, true, 3>), rows, dim3(64 * GW), 0, st, a);
         if (b1 < nt) {
             PushArgs pa;
             pa.m = m;

@@ -45,11 +45,12 @@ def test_gptq_shapes(oracle_mod, m, n):
 
 
 @pytest.mark.parametrize("rng_tiles,m,n", [(1, 65, 97), (3, 130, 257), (2, 257, 97), (5, 200, 300),
-                                             (1, 16, 70)])
+                                             (1, 16, 70), (40, 70, 1300)])
 def test_gptq_multi_range(oracle_mod, rng_tiles, m, n):
     """Column ranges of a few tiles (BAKRON_GPTQ_RANGE), so that small ragged
     shapes run several ranges and the pushes between them (partial last
-    range, partial row and column blocks of the push)."""
+    range, partial row and column blocks of the push); and one range longer
+    than 32 tiles, whose older errors are read back from memory."""
     p = _problem(m, n, seed=900 + rng_tiles + m + 3 * n)
     log(f"case one-sided m={m} n={n} range={rng_tiles} tiles")
     with _env(BAKRON_GPTQ_RANGE=rng_tiles):
@@ -99,6 +100,37 @@ def test_gptq_large_with_recursive_oracle(oracle_mod):
     log("case one-sided 1000x2080")
     codes, V, pre = gpu_run(p)
     check_against_oracle(p, codes, V, pre, oracle_mod, label="gptq-1000x2080", method="recursive")
+
+
+@pytest.mark.parametrize("general", [False, True])
+def test_gptq_rows_do_not_depend_on_row_count(general):
+    """The rows are independent, so a row's results are the same bits whichever
+    kernel its layer's row count picks: all errors in LDS (300 and 12300 rows: 19
+    and 769 workgroups) or the older ones from memory (8200 and 16400 rows: 513 and
+    1025).  35 column tiles: older errors, two ranges, a push."""
+    import torch
+    import paper_2608_06291_amd as pk
+    n = 1100
+    p = _problem(16, n, seed=66)
+    rng = np.random.default_rng(67)
+    W = torch.from_numpy((0.02 * rng.standard_normal((16400, n))).astype(np.float32)).to("cuda:0")
+    f = pk.factor(torch.from_numpy(p["A"]).to("cuda:0"), None, p["damp"])
+    kw, groups = {}, 1
+    if general:
+        groups = -(-n // 100)
+        kw = dict(alphabet="asym", group_size=100,
+                  col_scale=torch.from_numpy(rng.uniform(0.8, 1.25, n).astype(np.float32)).to("cuda:0"))
+    scale = torch.from_numpy(rng.uniform(0.005, 0.01, (16400, groups)).astype(np.float32)).to("cuda:0")
+    ref = None
+    for m in (300, 8200, 12300, 16400):
+        log(f"case one-sided rows m={m} general={general}")
+        out = [t[:300].cpu().numpy() for t in
+               pk.solve(W[:m], f, 4, scale[:m].reshape(-1).contiguous(), debug=True, **kw)[:3]]
+        if ref is None:
+            ref = out
+        for a, b in zip(out, ref):
+            assert np.array_equal(a, b)
+    f.close()
 
 
 @pytest.mark.parametrize("rng_tiles", [None, 2])
