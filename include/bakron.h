@@ -134,14 +134,15 @@ bakron_status bakron_factor(const float *A, int64_t n, const float *B, int64_t m
  * sets (the divide-and-conquer pushes into later segments overlap with the
  * segment launches), and joins back into `stream` with events.  It does so
  * for the shapes where a cost model of both schedules, built when the shape
- * is first planned, favours the overlap (near-square layers up to about
- * 4096 x 4096), always with the environment variable BAKRON_DEFER=1, and
- * never with BAKRON_DEFER=0.  When the cost model picks the two-stream plan
- * (BAKRON_DEFER unset), the first solve of that shape on the handle runs
- * both plans twice each, times them with events on `stream` (one host
- * synchronisation), keeps two streams for the handle if they are more than 3% faster, and returns the outputs
- * of its last run (not while per-launch profiling is enabled, which keeps
- * the model's choice).  On the legacy default stream, which
+ * is first planned, favours the overlap (with the present kernels it favours
+ * one stream on every shape measured, 1024 x 1024 to 14336 x 4096), always with
+ * the environment variable BAKRON_DEFER=1, and never with BAKRON_DEFER=0.  When
+ * the cost model picks the two-stream plan (BAKRON_DEFER unset), the first solve
+ * of that shape on the handle runs both plans twice each, times them with events
+ * on `stream` (one host synchronisation), keeps two streams for the handle if
+ * they are more than 3% faster, and returns the outputs of its last run (not
+ * while per-launch profiling is enabled, which keeps the model's choice).  On the
+ * legacy default stream, which
  * synchronises implicitly with such streams, and while `stream` is being
  * captured into a graph, everything runs on `stream`.  Unless
  * BAKRON_DEFER=0, the first solve planned on a device creates the two

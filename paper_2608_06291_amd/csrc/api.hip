@@ -605,13 +605,13 @@ static bool masked_streams(int device, int ncu, int R, hipStream_t* main, hipStr
 // a fixed latency.  A segment costs a fixed time per tile anti-diagonal (its
 // sequential chain); a node push a fixed launch cost plus its MFMA flops at
 // a per-CU rate on the CUs of its stream, a side push a larger fixed cost.
-// The constants are fitted to MI355X solve times of twelve layer shapes
-// (3072^2 to 14336 x 4096) under both plans, with earlier kernels (a tile
-// anti-diagonal of a segment now takes 11 us); only the comparison of the two
-// plans for one shape uses them, and a choice of two streams is timed.
+// The constants are fitted to MI355X solve times of sixteen layer shapes
+// (1024^2 to 14336 x 4096) under both plans; they meet them within 6% rms, and
+// the choice is the faster plan (or one within 1%) on all sixteen: one stream.
+// Only the comparison of the two plans for one shape uses them.
 static double plan_model_seconds(const bk::Plan& p, int cus_main, int cus_side) {
-    const double t_diag = 13.4e-6, t_seg = 3e-6, t_node = 6e-6, t_side = 30e-6, t_wait = 40e-6;
-    const double rate_cu = 0.45e12;
+    const double t_diag = 9.4e-6, t_seg = 3e-6, t_node = 14e-6, t_side = 34e-6, t_wait = 30e-6;
+    const double rate_cu = 0.55e12;
     std::vector<double> main_end(p.ops.size(), 0.0), side_end(p.side.size(), 0.0);
     double tm = 0.0, ts = 0.0;
     size_t next_side = 0;
@@ -655,6 +655,14 @@ static bool use_two_streams(const bk::Plan& one, const bk::Plan& two, int R, int
     // layers) one stream with every CU per push is faster
     return defer == 1 || plan_model_seconds(two, R, ncu - R) < plan_model_seconds(one, ncu, 0);
 }
+
+// Is the two-stream plan kept after both were timed (ms)?  Only if it is more than 3%
+// faster: two-stream solves of all handles share one pair of streams and run one
+// after the other, while one-stream solves on different streams overlap.  Measured (ms
+// per solve with one stream / two; a lone caller, then three handles on three streams in
+// turn): 3072^2 2.78 / 2.79 and 1.18 / 2.82, 4096^2 3.95 / 3.96 and 2.01 / 3.99, 4096 x
+// 3072 3.31 / 3.47 and 1.52 / 3.50; on no shape did two streams win.
+static bool keep_two_streams(float one_ms, float two_ms) { return one_ms > 1.03f * two_ms; }
 
 static bakron_status build_plan_entry(bakron_factors* f, int mt, int nt, int defer,
                                       PlanEntry& pe) {
@@ -976,13 +984,7 @@ static bakron_status solve_impl(const float* W, int64_t m, int64_t n, const bakr
                 if (e == hipSuccess && rep == 1) e = hipEventElapsedTime(&t[plan], f->tev[0], f->tev[1]);
             }
         if (e != hipSuccess) return hip_fail(&f->err, e, "bakron_solve: timing the plans");
-        // One stream from now on for this handle and shape, unless two are more
-        // than 3% faster: two-stream solves of all handles share one pair of
-        // streams and run one after the other, while one-stream solves on
-        // different streams overlap (4096 x 4096 alone: 3.94 ms with one stream,
-        // 3.93 with two; three handles on three streams in turn: 2.3 ms per solve
-        // with one, 3.9 with two).
-        if (t[0] <= 1.03f * t[1]) {
+        if (!keep_two_streams(t[0], t[1])) {   // one stream from now on for this handle and shape
             f->plan[1] = bk::Plan{};
             pi = 0;
         }

@@ -98,18 +98,22 @@ int main() {
     // MI355X for each shape (tiles of 32; solve ms with one stream / two):
     // 1 = two streams, 0 = one stream, -1 = within 1% (either is accepted)
     int shapes[][3] = {
-        {128, 128, 1},    // 4096 x 4096:   4.98 / 4.74
-        {96, 96, -1},     // 3072 x 3072:   3.52 / 3.48
-        {256, 64, 0},     // 8192 x 2048:   6.61 / 10.61
-        {64, 256, 0},     // 2048 x 8192:   6.54 / 10.54
-        {344, 128, 0},    // 11008 x 4096: 12.99 / 22.09
-        {128, 344, 0},    // 4096 x 11008: 12.77 / 20.29
-        {448, 128, 0},    // 14336 x 4096: 17.87 / 24.17
-        {128, 448, 0},    // 4096 x 14336: 17.24 / 27.96
-        {256, 128, 0},    // 8192 x 4096:   9.58 / 17.35
-        {128, 256, 0},    // 4096 x 8192:   9.48 / 14.51
-        {160, 160, 0},    // 5120 x 5120:   7.51 / 10.72
-        {192, 192, 0},    // 6144 x 6144:  10.23 / 22.86
+        {32, 32, 0},      // 1024 x 1024:   0.73 / 0.79
+        {47, 47, 0},      // 1500 x 1500:   1.17 / 1.27
+        {64, 64, 0},      // 2048 x 2048:   1.59 / 1.69
+        {96, 96, -1},     // 3072 x 3072:   2.78 / 2.79
+        {128, 96, 0},     // 4096 x 3072:   3.31 / 3.47
+        {128, 128, -1},   // 4096 x 4096:   3.95 / 3.96
+        {160, 160, 0},    // 5120 x 5120:   5.91 / 9.79
+        {192, 192, 0},    // 6144 x 6144:   7.88 / 19.13
+        {256, 64, 0},     // 8192 x 2048:   5.28 / 9.20
+        {64, 256, 0},     // 2048 x 8192:   5.28 / 9.19
+        {256, 128, 0},    // 8192 x 4096:   7.49 / 11.81
+        {128, 256, 0},    // 4096 x 8192:   7.52 / 13.40
+        {344, 128, 0},    // 11008 x 4096: 10.18 / 16.24
+        {128, 344, 0},    // 4096 x 11008: 10.17 / 19.16
+        {448, 128, 0},    // 14336 x 4096: 13.62 / 22.74
+        {128, 448, 0},    // 4096 x 14336: 13.63 / 26.75
         {896, 256, 0},    // 28672 x 8192: the widest segment needs every CU
     };
     for (auto& sh : shapes) {
@@ -126,6 +130,19 @@ int main() {
             printf("cost model picks the slower plan for %dx%d tiles\n", sh[0], sh[1]);
             ++fails;
         }
+    }
+    // a shape that the model gives to two streams (by 1%), so that its first solve times both
+    {
+        bk::Plan p0, p1; std::vector<int4> it;
+        build_plan(69, 75, 8, 0, false, p0, it);
+        build_plan(69, 75, 8, 0, true, p1, it);
+        if (!use_two_streams(p0, p1, side_split(p0, 256), 256, 2)) { printf("2208 x 2400 is not timed\n"); ++fails; }
+    }
+    // after a timing: two streams only where they are more than 3% faster
+    if (keep_two_streams(3.95f, 3.96f) || keep_two_streams(4.0f, 4.0f) || keep_two_streams(4.10f, 4.0f) ||
+        !keep_two_streams(4.13f, 4.0f)) {
+        printf("keep_two_streams\n");
+        ++fails;
     }
     printf("fails %d\n", fails);
     return fails;

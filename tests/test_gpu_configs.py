@@ -111,13 +111,16 @@ def test_config_shape_ar1_exact(oracle_mod, cid):
 
 
 @pytest.mark.timeout(600)
-def test_config2_two_stream_plan_bitwise():
-    """The 4096x4096 layer on a stream of its own (node pushes overlapped on the
-    side stream) and on the legacy default stream (everything on one stream):
-    bitwise identical codes, V and pre-rounding values."""
+def test_config2_two_stream_plan_bitwise(monkeypatch):
+    """The 4096x4096 layer on a stream of its own with the two-stream plan
+    (BAKRON_DEFER=1: node pushes overlapped on the side stream) and on the legacy
+    default stream (everything on one stream): bitwise identical codes, V and
+    pre-rounding values."""
     c = workloads.make(2, seed=0, device="cuda")
     log("case config 2 two-stream vs one-stream plan")
+    monkeypatch.setenv("BAKRON_DEFER", "1")
     c1, v1, x1 = _run(c, True)
+    monkeypatch.delenv("BAKRON_DEFER")
     c0, v0, x0 = gpu_run(c, debug=True)
     assert np.array_equal(c0, c1)
     assert np.array_equal(v0.view(np.uint32), v1.view(np.uint32))

@@ -151,6 +151,22 @@ def test_side_stream_bitwise(m, n, k):
         assert np.array_equal(x0.view(np.uint32), x.view(np.uint32))
 
 
+def test_first_solve_timing_bitwise(monkeypatch):
+    """A shape for which the cost model picks two streams: the first solve on a
+    stream of its own runs and times both plans, a later one the plan kept; both
+    return the bits of the one-stream plan (the legacy default stream)."""
+    import torch
+    monkeypatch.delenv("BAKRON_DEFER", raising=False)
+    p = _problem(2208, 2400, seed=93)
+    log("case first-solve timing 2208x2400")
+    ref = gpu_run(p)
+    with torch.cuda.stream(torch.cuda.Stream()):
+        got = gpu_run(p, repeat=2)
+    for out in got:
+        for a, b in zip(out, ref):
+            assert np.array_equal(a, b, equal_nan=a.dtype.kind == "f")
+
+
 @pytest.mark.parametrize("m,n,k,identity_B", [(257, 129, None, False), (100, 97, 0, False),
                                                (130, 70, 3, True)])
 def test_poisoned_workspace_bitwise(m, n, k, identity_B):
