@@ -95,10 +95,8 @@ __global__ __launch_bounds__(64 * GW, WG) void k_gptq(GptqArgs a) {
     // are read while the block before it is rounded
     // (block bn, source tile kt; an old tile's errors were written RT blocks ago)
     f32x4 f[2][4], eo[2][2];
-    const float* const lrow = a.LA + i16 * TS + 8 * s;
     const float* const erow = a.E + (row0 + i16) * a.ldE + 8 * s;
-    auto ldf = [&](int bn, int kt, int q) {
-        const float* p = lrow + packed_tile_offset(bn, kt);
+    auto ldf = [&](const float* p, int bn, int kt, int q) {
         f[q][0] = ld4(p);
         f[q][1] = ld4(p + 4);
         f[q][2] = ld4(p + 16 * TS);
@@ -131,6 +129,7 @@ __global__ __launch_bounds__(64 * GW, WG) void k_gptq(GptqArgs a) {
         // ..., set 1 tiles w + GW, w + 3 GW, ...; the errors are in LDS
         f32x4 acc0 = {0.0f, 0.0f, 0.0f, 0.0f}, acc1 = {0.0f, 0.0f, 0.0f, 0.0f};
         {
+            const float* lt = a.LA + packed_tile_offset(b, 0) + i16 * TS + 8 * s;
             auto mul = [&](int kt, int q) {
                 f32x4 x0 = eo[q][0], x1 = eo[q][1];
                 if (!OLD || kt >= b - RT) {   // uniform
@@ -144,9 +143,9 @@ __global__ __launch_bounds__(64 * GW, WG) void k_gptq(GptqArgs a) {
             int kt = a.b_begin + w;
             for (; kt + GW < b; kt += 2 * GW) {
                 mul(kt, 0);
-                if (kt + 2 * GW < b) ldf(b, kt + 2 * GW, 0);
+                if (kt + 2 * GW < b) ldf(lt + (kt + 2 * GW) * TILE_ELEMS, b, kt + 2 * GW, 0);
                 mul(kt + GW, 1);
-                if (kt + 3 * GW < b) ldf(b, kt + 3 * GW, 1);
+                if (kt + 3 * GW < b) ldf(lt + (kt + 3 * GW) * TILE_ELEMS, b, kt + 3 * GW, 1);
             }
             if (kt < b) mul(kt, 0);
         }
@@ -176,9 +175,10 @@ __global__ __launch_bounds__(64 * GW, WG) void k_gptq(GptqArgs a) {
             c1[j] = j < 16 + c16 ? u1[j >> 2][j & 3] : 0.0f;
         }
         if (b + 1 < a.b_end) {
+            const float* lt = a.LA + packed_tile_offset(b + 1, 0) + i16 * TS + 8 * s;
             const int kt = a.b_begin + w;
-            if (kt <= b) ldf(b + 1, kt, 0);
-            if (kt + GW <= b) ldf(b + 1, kt + GW, 1);
+            if (kt <= b) ldf(lt + kt * TILE_ELEMS, b + 1, kt, 0);
+            if (kt + GW <= b) ldf(lt + (kt + GW) * TILE_ELEMS, b + 1, kt + GW, 1);
         }
         float e0 = 0.0f, e1 = 0.0f, x0 = 0.0f, x1 = 0.0f;
         auto column = [&](auto C) {
