@@ -214,8 +214,11 @@ static void leaves(int K, int L, int knear, std::vector<std::pair<int, int>>& ou
 // and 64 x 64 with at least NODE_MIN_ITEMS items (a wider block reads its
 // operands less often and splits them for more products; with fewer items the
 // last round leaves most CUs idle); 8, 4 or 2 forces one size.
-// The nodes of at most NODE32_SPAN tile anti-diagonals go to the fp32 kernel.  The rule looks at the node, not at the push, so that the one- and
-// the two-stream plan, which cut a node's push differently, give the same bits.
+// The nodes of at most NODE32_SPAN tile anti-diagonals go to the fp32 kernel (k_node32
+// has the times of both; the levels of a plan have spans of about 2^k 9, so the line
+// lies between 32 to 36 and 58 to 72).  The rule looks at the node, not at the push,
+// so that the one- and the two-stream plan, which cut a node's push differently, give
+// the same bits.
 constexpr int NODE_MIN_ITEMS = 512;
 constexpr int NODE32_SPAN = 36;
 static bool node_op(int K, int Mid, int L, int tlo, int thi, int mt, int nt, int knear, int b_ident,

@@ -791,7 +791,7 @@ struct NodeArgs {
 // 28672 x 8192 layer 65.0 -> 53.0 ms (129 -> 159 TFLOP/s of fp32 products), of
 // 11008 x 4096 5.6 -> 5.0.
 template <int MT>
-__global__ __launch_bounds__(SplitShape<MT>::TH, (MT == 2 ? 4 : 2)) void k_node(NodeArgs a) {
+__global__ __launch_bounds__(SplitShape<MT>::TH, 2) void k_node(NodeArgs a) {
     using C = SplitShape<MT>;
     __shared__ __attribute__((aligned(16))) uint16_t S[C::LDS];
     const int4 it = a.items[blockIdx.x];
@@ -872,9 +872,13 @@ __global__ __launch_bounds__(SplitShape<MT>::TH, (MT == 2 ? 4 : 2)) void k_node(
 
 // The same push on fp32 MFMA, 64 x 64 per workgroup: for the nodes of at most
 // NODE32_SPAN tile anti-diagonals.  Their source ranges are so short that the
-// launch is bound by latency and operand bytes; the split's conversions only
-// add to it (a launch of the 18-diagonal nodes of the 1024 x 1024 layer takes
-// 13 us here, 15 with k_node<2>).  4 waves in a 2 x 2 arrangement; inside a K chunk
+// launch is bound by latency and operand bytes, and the split's conversions and
+// the third more LDS bytes of its planes only add to it.  us per launch here / with
+// k_node<2>: nodes of 15, 16, 31, 32 anti-diagonals of the 1024 x 1024 layer 6.9 /
+// 7.8, 8.1 / 9.5, 12.9 / 14.5, 13.8 / 15.8, of the 4096 x 4096 layer 7.5 / 7.9, 10.2 /
+// 11.1, 14.1 / 14.7, 26.1 / 27.5; from 58 to 64 anti-diagonals the two are within 6%
+// (4096 x 4096: 29.1 / 30.5 and 77.7 / 77.4), and the split is the more exact one.
+// 4 waves in a 2 x 2 arrangement; inside a K chunk
 // the 32 k's are split between the two lane halves (half h takes k = 16h + s at
 // step s), so each lane reads 16 consecutive floats per operand with four
 // 16-byte LDS loads.  LDS is double buffered and the chunks two ahead are
