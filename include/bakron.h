@@ -249,7 +249,10 @@ bakron_status bakron_mse_scales(const float *W, int64_t m, int64_t n, int32_t bi
  * launch); the results are unchanged, which shows that no workspace word is
  * read before the solve writes it.  BAKRON_SPIN_LIMIT=k (1 <= k <= 2^22),
  * read at every solve, lowers the number of polls after which a tile-ordering
- * wait gives up, to exercise that path (bakron_solve_check) from the host. */
+ * wait gives up, to exercise that path (bakron_solve_check) from the host.
+ * BAKRON_LATE=b (1..3, read at handle creation) makes the tiles of a solve treat the
+ * strip two to their left (bit 0) or those further left (bit 1) as late, which
+ * exercises the staging for that case; the results are unchanged. */
 
 /* Frees the handle, its factors and its workspace (synchronises the device
  * work that used them).  NULL is a no-op. */

@@ -29,7 +29,7 @@ hipError_t unpack_factor(hipStream_t s, const float* packed, int64_t d, float* d
 hipError_t run_plan(hipStream_t st, hipStream_t side, const Plan& plan, const float* W, int64_t m,
                     int64_t n, int mt, int nt, const Workspace& ws, const float* LA, const float* LB,
                     int b_ident, const QuantArgs& q, int8_t* codes, float* V, float* pre,
-                    int knear, int spin_limit, const int4* items, hipEvent_t* tim,
+                    int knear, int spin_limit, int late, const int4* items, hipEvent_t* tim,
                     hipEvent_t* ev_rel, hipEvent_t* ev_side);
 hipError_t check_scales(hipStream_t st, const float* s, int64_t count, int* bad);
 int plan_timed_launches(const Plan& plan);
@@ -54,6 +54,10 @@ struct bakron_factors {
     void* ws_mem = nullptr;         // X, Y tile arrays, flags, counters, status (bk::Workspace)
     bk::Workspace ws{};
     int knear = 8;
+    // BAKRON_LATE (1..3) at creation: bit 0 makes every tile find the strip two to its
+    // left late, bit 1 those further left, so that it stages their errors itself
+    // instead of beside the tile above (debug aid: the results do not change)
+    int late = 0;
     // node macro tile: 0 per node (default), 8, 4 or 2 forced (BAKRON_MACRO)
     int macro = 0;
     // BAKRON_POISON=1 at creation: fill the workspace with NaN / -1 before
@@ -357,6 +361,7 @@ extern "C" bakron_status bakron_factor(const float* A, int64_t n, const float* B
     f->b_ident = B ? 0 : 1;
     f->damp = damp;
     if (const char* pz = std::getenv("BAKRON_POISON")) f->poison = std::atoi(pz) != 0;
+    if (const char* lt = std::getenv("BAKRON_LATE")) f->late = std::atoi(lt) & 3;
     if (const char* kn = std::getenv("BAKRON_KNEAR")) {
         int v = std::atoi(kn);
         if (v >= 0 && v <= bk::KNEAR_MAX) f->knear = v;
@@ -965,7 +970,7 @@ static bakron_status solve_impl(const float* W, int64_t m, int64_t n, const bakr
         }
         if (e == hipSuccess)
             e = bk::run_plan(ms, f->side, f->plan[plan], W, m, n, mt, nt, f->ws, f->LA, f->LB,
-                             f->b_ident, qa, codes, V, pre, f->knear, spin_limit, f->items,
+                             f->b_ident, qa, codes, V, pre, f->knear, spin_limit, f->late, f->items,
                              plan == pi ? tim : nullptr, f->ev_rel.data(), f->ev_side.data());
         if (fork && e == hipSuccess) {
             e = hipEventRecord(f->ev_join, ms);
@@ -1204,7 +1209,7 @@ extern "C" bakron_status bakron_solve_noalloc(const float* W, int64_t m, int64_t
     }
     if (e == hipSuccess)
         e = bk::run_plan(stream, nullptr, hp->plan, W, m, n, mt, nt, ws, f->LA, f->LB, f->b_ident,
-                         quant_args(q, n), codes, V, nullptr, f->knear, spin_limit, items, nullptr,
+                         quant_args(q, n), codes, V, nullptr, f->knear, spin_limit, 0, items, nullptr,
                          nullptr, nullptr);
     if (e != hipSuccess) return hip_fail(&f->err, e, "bakron_solve_noalloc: launch");
     f->noalloc_used = 1;

@@ -62,6 +62,7 @@ struct SegArgs {
     int* counter;     // strip ticket counter of this launch, 0 at entry
     int* status;      // set to 1 if a wait gave up (never in a correct run); sticky
     int spin_limit;   // polls before a wait gives up
+    int late;         // debug (LATE): bit k - 2 set: the poll for F[., J-k] finds it not ready
 };
 
 // Bounded wait for a tile's ready flag to reach `level`, executed by a whole
@@ -181,6 +182,7 @@ constexpr int RSTR = TS + 4;      // LDS row stride: 16-byte rows, conflict-free
 //     pre.  The service waves do this beside the next tile's start.
 // GQ: scales per column group and/or per column (else one scale per row).
 // ASYM: alphabet {qlo..qhi} (else the symmetric {-qhi..qhi}).
+// LATE: a.late holds (a debug switch; one instance, for every quantiser).
 constexpr int SEG_THREADS = 768;
 constexpr int SG = 8;                                  // anti-diagonals per group
 constexpr int NGRP = (2 * TS - 1 + SG - 1) / SG;       // groups per tile
@@ -232,7 +234,7 @@ __device__ inline void seg_sync() {
 // three; what a role does not do is removed at compile time, so that the
 // registers of the roles are not live at once).  W: the wave's number within
 // its role.
-template <bool GQ, bool ASYM, int ROLE>
+template <bool GQ, bool ASYM, bool LATE, int ROLE>
 __device__ __forceinline__ void seg_role(const SegArgs& a, float* sm, int& tk, volatile int* yready, int w, int W) {
     const int tid = threadIdx.x, l = tid & 63;
     const int hf = l >> 5, p = l & 31;
@@ -502,7 +504,7 @@ __device__ __forceinline__ void seg_role(const SegArgs& a, float* sm, int& tk, v
             auto poll = [&](int k) {
                 if (sv == 2 && l == 0)
                     yready[k - 2] = kr < k || __hip_atomic_load(a.flags + (I + 1) * a.nt + (J - k), __ATOMIC_RELAXED,
-                                                                __HIP_MEMORY_SCOPE_AGENT) >= 2;
+                                                                __HIP_MEMORY_SCOPE_AGENT) >= 2 + (LATE ? a.late >> (k - 2) & 1 : 0);
             };
             if (has_next) poll(3);
             seg_sync();
@@ -715,14 +717,14 @@ __device__ __forceinline__ void seg_role(const SegArgs& a, float* sm, int& tk, v
 
 // Wave i runs on SIMD i mod 4: the solver shares its SIMD with two service waves
 // only (beside pull waves its steps took a third longer).
-template <bool GQ, bool ASYM>
+template <bool GQ, bool ASYM, bool LATE>
 __global__ __launch_bounds__(SEG_THREADS) void k_seg(SegArgs a) {
     __shared__ __attribute__((aligned(16))) float sm[GQ ? S_END_GQ : S_END];
     __shared__ int tk, yready[2];
     const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    if (w == 0) seg_role<GQ, ASYM, SOLVER>(a, sm, tk, yready, w, 0);
-    else if (w == 4 || w == 8 || w == 11) seg_role<GQ, ASYM, SERVICE>(a, sm, tk, yready, w, w >> 2 == 1 ? 0 : w == 8 ? 1 : 2);
-    else seg_role<GQ, ASYM, PULL>(a, sm, tk, yready, w, w - 1 - (w > 4) - (w > 8));
+    if (w == 0) seg_role<GQ, ASYM, LATE, SOLVER>(a, sm, tk, yready, w, 0);
+    else if (w == 4 || w == 8 || w == 11) seg_role<GQ, ASYM, LATE, SERVICE>(a, sm, tk, yready, w, w >> 2 == 1 ? 0 : w == 8 ? 1 : 2);
+    else seg_role<GQ, ASYM, LATE, PULL>(a, sm, tk, yready, w, w - 1 - (w > 4) - (w > 8));
 }
 
 // Fills n 32-bit words with v (a debug aid: poisoning the workspace before a
@@ -1089,7 +1091,7 @@ __global__ __launch_bounds__(256) void k_prep(const float* __restrict__ W, int64
 hipError_t run_plan(hipStream_t st, hipStream_t side, const Plan& plan, const float* W, int64_t m,
                     int64_t n, int mt, int nt, const Workspace& ws, const float* LA, const float* LB,
                     int b_ident, const QuantArgs& q, int8_t* codes, float* V, float* pre,
-                    int knear, int spin_limit, const int4* items, hipEvent_t* tim,
+                    int knear, int spin_limit, int late, const int4* items, hipEvent_t* tim,
                     hipEvent_t* ev_rel, hipEvent_t* ev_side) {
     int ti = 0;
     auto t_begin = [&](hipStream_t s) { if (tim) (void)hipEventRecord(tim[2 * ti], s); };
@@ -1111,6 +1113,7 @@ hipError_t run_plan(hipStream_t st, hipStream_t side, const Plan& plan, const fl
     sa.codes = codes; sa.V = V; sa.pre = pre; sa.knear = knear; sa.flags = ws.flags;
     sa.status = ws.status;
     sa.spin_limit = spin_limit;
+    sa.late = late;
     NodeArgs nd{};
     nd.knear = knear; nd.mt = mt; nd.nt = nt; nd.X = ws.X; nd.Y = ws.Y; nd.LA = LA; nd.LB = LB;
     auto node = [&](const PlanOp& op, hipStream_t s) {
@@ -1146,14 +1149,16 @@ hipError_t run_plan(hipStream_t st, hipStream_t side, const Plan& plan, const fl
                 sa.counter = ws.counters + op.counter;
                 const int grid = op.nstrips < SEG_GRID ? op.nstrips : SEG_GRID;
                 const bool gq = q.gsize > 0 || q.col_scale, asym = q.qlo != -q.qhi;
-                if (gq && asym)
-                    hipLaunchKernelGGL((k_seg<true, true>), dim3((unsigned)grid), dim3(SEG_THREADS), 0, st, sa);
+                if (late)
+                    hipLaunchKernelGGL((k_seg<true, true, true>), dim3((unsigned)grid), dim3(SEG_THREADS), 0, st, sa);
+                else if (gq && asym)
+                    hipLaunchKernelGGL((k_seg<true, true, false>), dim3((unsigned)grid), dim3(SEG_THREADS), 0, st, sa);
                 else if (gq)
-                    hipLaunchKernelGGL((k_seg<true, false>), dim3((unsigned)grid), dim3(SEG_THREADS), 0, st, sa);
+                    hipLaunchKernelGGL((k_seg<true, false, false>), dim3((unsigned)grid), dim3(SEG_THREADS), 0, st, sa);
                 else if (asym)
-                    hipLaunchKernelGGL((k_seg<false, true>), dim3((unsigned)grid), dim3(SEG_THREADS), 0, st, sa);
+                    hipLaunchKernelGGL((k_seg<false, true, false>), dim3((unsigned)grid), dim3(SEG_THREADS), 0, st, sa);
                 else
-                    hipLaunchKernelGGL((k_seg<false, false>), dim3((unsigned)grid), dim3(SEG_THREADS), 0, st, sa);
+                    hipLaunchKernelGGL((k_seg<false, false, false>), dim3((unsigned)grid), dim3(SEG_THREADS), 0, st, sa);
             } else {
                 node(op, st);
             }

@@ -151,6 +151,28 @@ def test_side_stream_bitwise(m, n, k):
         assert np.array_equal(x0.view(np.uint32), x.view(np.uint32))
 
 
+@pytest.mark.parametrize("late", [1, 2, 3])
+@pytest.mark.parametrize("m,n,k,general", [(300, 420, 8, False), (700, 330, 8, True), (260, 500, 3, False),
+                                           (130, 170, 2, False)])
+def test_late_left_strips_bitwise(monkeypatch, m, n, k, general, late):
+    """BAKRON_LATE makes every tile treat the strip two to its left (bit 0) or those
+    further left (bit 1) as late: it then waits for them and stages their F itself
+    instead of beside the tile above it.  The sums keep their order, so every bit
+    stays the same."""
+    p = _problem(m, n, seed=m + 5 * n)
+    if general:
+        r = np.random.default_rng(8)
+        p["scale"] = (p["scale"][:, None] * r.uniform(0.6, 1.4, (m, -(-n // 32)))).astype(np.float32)
+        p.update(group_size=32, alphabet="asym", col_scale=r.uniform(0.8, 1.25, n).astype(np.float32))
+    log(f"case late left strips m={m} n={n} knear={k} late={late}")
+    monkeypatch.delenv("BAKRON_LATE", raising=False)
+    ref = gpu_run(p, k=k)
+    monkeypatch.setenv("BAKRON_LATE", str(late))
+    got = gpu_run(p, k=k)
+    for a, b in zip(got, ref):
+        assert np.array_equal(a, b, equal_nan=a.dtype.kind == "f")
+
+
 def test_first_solve_timing_bitwise(monkeypatch):
     """A shape for which the cost model picks two streams: the first solve on a
     stream of its own runs and times both plans, a later one the plan kept; both
