@@ -123,6 +123,11 @@ bakron_status bakron_factor(const float *A, int64_t n, const float *B, int64_t m
  *   codes  device, m x n int8 output in the alphabet
  *   V      device, m x n fp32 output, V_ij = s_ij * codes_ij (one fp32 product)
  *
+ * A non-finite weight, or one so large that products with it overflow, reaches
+ * the entries that depend on it (those below and to the right; with B = I the
+ * rest of its row): their codes stay in the alphabet and V = s * code, but what
+ * they are is unspecified.  All other entries are not touched by it.
+ *
  * The first call for a given (m, n) allocates the workspace (about 8*m*n
  * bytes plus one int per 32 x 32 tile) and builds the launch plans (and may
  * synchronise the host, see below); later calls with the same (m, n)

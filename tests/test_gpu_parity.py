@@ -151,6 +151,28 @@ def test_side_stream_bitwise(m, n, k):
         assert np.array_equal(x0.view(np.uint32), x.view(np.uint32))
 
 
+@pytest.mark.parametrize("value", [float("inf"), float("-inf"), float("nan"), 1e38])
+@pytest.mark.parametrize("m,n,one_sided", [(1300, 1300, False), (300, 420, False), (200, 2500, True)])
+def test_non_finite_weight_stays_downstream(m, n, one_sided, value):
+    """An infinite, NaN or overflowing weight at (100, 200) reaches the entries below
+    and to the right of it (its row only, if B = I); all others keep their bits, and
+    every code stays in the alphabet with V = s c.  1300 x 1300 pushes with the split
+    product, 300 x 420 in fp32 only, 200 x 2500 between two ranges."""
+    p = _problem(m, n, seed=m + 7 * n, identity_B=one_sided)
+    log(f"case weight {value} m={m} n={n} one-sided={one_sided}")
+    ref = gpu_run(p)
+    W = p["W"].copy()
+    W[100, 200] = value
+    got = gpu_run(dict(p, W=W))
+    keep = np.ones((m, n), bool)
+    keep[100:101 if one_sided else m, 200:] = False
+    for a, b in zip(got, ref):
+        assert np.array_equal(a[keep], b[keep])
+    codes, V, _ = got
+    assert np.abs(codes.astype(np.int32)).max() <= 7
+    assert np.array_equal(V, (p["scale"][:, None] * codes.astype(np.float32)).astype(np.float32))
+
+
 @pytest.mark.parametrize("late", [1, 2, 3])
 @pytest.mark.parametrize("m,n,k,general", [(300, 420, 8, False), (700, 330, 8, True), (260, 500, 3, False),
                                            (130, 170, 2, False)])
