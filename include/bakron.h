@@ -291,6 +291,8 @@ bakron_status bakron_factor_export(const bakron_factors *f, int which, float *ds
  *   1 segment: rounding of the tiles of a range of tile anti-diagonals
  *     (Alg. 6 leaves and the lowest recursion levels), near field included
  *   2 node push: divide-and-conquer band update (Alg. 6 internal nodes)
+ *   3 of those, the pushes of short nodes, which run on fp32 MFMA; the others of
+ *     class 2 run six bf16 products for each fp32 product
  * with
  *   ms          summed launch durations
  *   launches    number of launches
@@ -298,7 +300,7 @@ bakron_status bakron_factor_export(const bakron_factors *f, int which, float *ds
  *               fed back (Eq. (1)), plus the in-tile pairs of solved tiles;
  *               for class 0, bytes moved instead
  *   mfma_flops  flops of the fp32 products executed on the matrix cores, zero-masked
- *               tiles included (a node push executes six bf16 products for each)
+ *               tiles included
  * Classes beyond nstats are dropped.  Returns BAKRON_EINVAL if no profiled
  * solve has been enqueued since enabling.
  */
@@ -371,11 +373,14 @@ bakron_status bakron_solve_noalloc(const float *W, int64_t m, int64_t n, const b
  *
  * Conventions of this group (in addition to those above):
  *   - sample matrices are N x d row-major fp32, one sample per row;
- *   - computed on the matrix cores at fp32 precision (three-way bf16 split of the
- *     operands, fp32 sums; plain fp32 products for sums of at most 4 terms and for
- *     results that are not finite, which are those of fp32 arithmetic); the
- *     summation order is fixed for a given device and shape, so repeated calls
- *     give bitwise the same result;
+ *   - computed on the matrix cores as fp32 products split into six bf16 products,
+ *     summed in fp32: a single product is within 3 u of its size (u = 2^-24, fp32's
+ *     half ulp), sums of 3 or 4 and more terms are nearer to exact than those of
+ *     fp32 products; plain fp32 products for sums of at most 4 terms and for
+ *     results that are not finite, which are those of fp32 arithmetic.  Entries
+ *     below 2^-110 in size are kept to within 2^-133.  The summation order is
+ *     fixed for a given device and shape, so repeated calls give bitwise the same
+ *     result;
  *   - workspace protocol: with work == NULL the call stores the number of
  *     workspace bytes it needs in *work_bytes and does nothing else (no GPU
  *     work, pointers not checked); otherwise work is a device buffer of

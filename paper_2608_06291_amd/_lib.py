@@ -171,13 +171,20 @@ class Factors:
 
     PROFILE_CLASSES = ("prep", "segment", "node")
 
-    def profile_read(self):
-        """Per-class stats of the last profiled solve (stream must be synchronised)."""
-        arr = (KernelStat * len(self.PROFILE_CLASSES))()
-        st = load().bakron_profile_read(self._h, arr, len(self.PROFILE_CLASSES))
+    def _profile_stats(self):
+        arr = (KernelStat * 4)()
+        st = load().bakron_profile_read(self._h, arr, 4)
         if st != BAKRON_OK:
             raise BakronError(st, self.error())
-        return {k: arr[i].as_dict() for i, k in enumerate(self.PROFILE_CLASSES)}
+        return [a.as_dict() for a in arr]
+
+    def profile_read(self):
+        """Per-class stats of the last profiled solve (stream must be synchronised)."""
+        return dict(zip(self.PROFILE_CLASSES, self._profile_stats()))
+
+    def profile_read_node_fp32(self):
+        """The part of profile_read()["node"] that ran on fp32 MFMA (short nodes)."""
+        return self._profile_stats()[3]
 
     def check(self) -> bool:
         """True if every solve on this handle since the last check completed

@@ -799,7 +799,7 @@ static bakron_status ensure_workspace(bakron_factors* f, int64_t m, int64_t n) {
         f->tmfma[pi].assign(1, 0.0);
         for (const std::pair<int, int>& o : pl.order) {
             const bk::PlanOp& op = o.first == 0 ? pl.ops[o.second] : pl.side[o.second];
-            f->tclass[pi].push_back(op.kind == 0 ? 1 : 2);
+            f->tclass[pi].push_back(op.kind == 0 ? 1 : op.fp32 ? 3 : 2);
             f->tflops[pi].push_back(op.flops);
             f->tmfma[pi].push_back(op.mfma_flops);
         }
@@ -1086,12 +1086,13 @@ extern "C" bakron_status bakron_profile_read(const bakron_factors* f, bakron_ker
         hipError_t e = hipEventElapsedTime(&ms, f->tim[2 * i], f->tim[2 * i + 1]);
         if (e != hipSuccess)
             return hip_fail(&const_cast<bakron_factors*>(f)->err, e, "bakron_profile_read");
-        const int k = f->tclass[pi][i];
-        if (k >= nstats) continue;
-        stats[k].ms += ms;
-        stats[k].launches += 1;
-        stats[k].flops += f->tflops[pi][i];
-        stats[k].mfma_flops += f->tmfma[pi][i];
+        const int c = f->tclass[pi][i];
+        for (int k = c == 3 ? 2 : c; k <= c && k < nstats; ++k) {   // class 3 is part of class 2
+            stats[k].ms += ms;
+            stats[k].launches += 1;
+            stats[k].flops += f->tflops[pi][i];
+            stats[k].mfma_flops += f->tmfma[pi][i];
+        }
     }
     return BAKRON_OK;
 }

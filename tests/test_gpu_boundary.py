@@ -103,6 +103,28 @@ def test_give_up_record_is_sticky_until_checked(oracle_mod):
     f.close()
 
 
+@pytest.mark.parametrize("m,n", [(300, 420), (1300, 1300)])
+def test_profile_prices_fp32_and_split_pushes_apart(m, n):
+    """Class 3 of the measurement hook is the part of class 2 that runs on fp32 MFMA:
+    all pushes of a layer of at most 36 tile anti-diagonals (300 x 420: 23), some of a
+    larger one's (1300 x 1300: 81)."""
+    import torch
+    log(f"case profile classes m={m} n={n}")
+    p, f, W, s = _setup(m, n, seed=35)
+    import paper_2608_06291_amd as pk
+    f.profile(True)
+    pk.solve(W, f, p["bits"], s)
+    torch.cuda.synchronize()
+    node, fp32 = f.profile_read()["node"], f.profile_read_node_fp32()
+    assert 0 < fp32["launches"] <= node["launches"] and 0 < fp32["ms"] <= node["ms"]
+    if m == 300:
+        assert fp32 == node
+    else:
+        assert fp32["launches"] < node["launches"] and fp32["flops"] < node["flops"]
+        assert fp32["mfma_flops"] < node["mfma_flops"]
+    f.close()
+
+
 def test_two_handles_on_two_streams_bitwise():
     """Two handles (two shapes) solved on two user streams, their solves
     enqueued back to back with no synchronisation in between: both share the
