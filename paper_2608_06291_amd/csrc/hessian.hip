@@ -107,9 +107,10 @@ __global__ __launch_bounds__(256) void k_diag(const float* __restrict__ src, int
 // [plane][feature][sample].  LDS double-buffered, the next chunk in registers
 // while the current one is multiplied.
 // GT = 256: 8 waves of 128 x 64, one workgroup per CU (144 KiB of LDS);
-// GT = 128: 4 waves of 64 x 64, two workgroups per CU.  What bounds it: the
-// bf16 matrix cores at the clock they hold (the wide block needs 62% of the
-// LDS and a quarter of the VALU cycles of its MFMA time).  Measured, 524288
+// GT = 128: 4 waves of 64 x 64, two workgroups per CU.  What limits it
+// (counters, 4096 features): no single unit.  The matrix cores are busy 56% of the
+// cycles at the 2.0 GHz that the chip holds under this load, the LDS 24%, HBM delivers
+// 0.6 TB/s; the one workgroup of a CU meets at a barrier per chunk.  Measured, 524288
 // samples: 4096 features 79.8 -> 48.6 ms (110 -> 181 TFLOP/s) against the
 // same product on fp32 MFMA, with a relative error against 64 bits of 5e-7
 // instead of 3.8e-6; 400 features 1.58 -> 0.99 ms; rows that are not 16-byte

@@ -160,9 +160,9 @@ constexpr int RSTR = TS + 4;      // LDS row stride: 16-byte rows, conflict-free
 // sources, a smaller one more barriers and less time for the pull waves: SG = 7
 // made the segments of the 4096 x 4096 layer 8% longer, SG = 4 37%.
 // Measured against the kernel before it, in which all eight waves took turns
-// at the rounding and met at a barrier per 4 anti-diagonals: 12.7 -> 10.7 us
-// per tile anti-diagonal (4096 x 4096), 13.3 -> 11.2 (28672 x 8192), the 64 x 64
-// layer 34.6 -> 29.9 us in all.  Of a tile's 23000 cycles 2600 go to the sums
+// at the rounding and met at a barrier per 4 anti-diagonals: 12.8 -> 10.5 us
+// per tile anti-diagonal (4096 x 4096, kernel trace), 13.2 -> 11.4 (28672 x 8192), the
+// 64 x 64 layer 34.5 -> 28.6 us in all.  Of a tile's 23000 cycles 2600 go to the sums
 // of the block at its origin before the solver can start (flag and F of the
 // left tile), 17100 to its steps, the rest to waiting for the pull waves of the
 // blocks with the most pushes.
@@ -788,10 +788,12 @@ struct NodeArgs {
 //
 // One workgroup per work-list item (MT x MT solver tiles): the host lists only
 // items with a non-empty source range, longest first, so the long K loops
-// start early.  Bound by the matrix cores and the power they draw on the large
-// nodes; measured against the fp32 MFMA kernel before it: all pushes of the
-// 28672 x 8192 layer 65.0 -> 53.0 ms (129 -> 159 TFLOP/s of fp32 products), of
-// 11008 x 4096 5.6 -> 5.0.
+// start early.  What limits the large pushes (counters, <8> on the 28672 x 8192
+// layer): no single unit.  The matrix cores are busy 54% of the cycles, the LDS 24%,
+// HBM delivers 2.0 TB/s; the chip holds 1.9 GHz under this load (of 2.4), which is
+// what a power limit looks like, and the one workgroup of a CU meets at a barrier per
+// chunk.  Measured against fp32 MFMA: all pushes of that layer
+// 65.0 -> 53.0 ms (129 -> 159 TFLOP/s of fp32 products), of 11008 x 4096 5.6 -> 5.0.
 template <int MT>
 __global__ __launch_bounds__(SplitShape<MT>::TH, 2) void k_node(NodeArgs a) {
     using C = SplitShape<MT>;
