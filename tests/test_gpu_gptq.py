@@ -102,28 +102,29 @@ def test_gptq_large_with_recursive_oracle(oracle_mod):
     check_against_oracle(p, codes, V, pre, oracle_mod, label="gptq-1000x2080", method="recursive")
 
 
+@pytest.mark.parametrize("n,rows", [(1100, (300, 8200, 12300, 16400)), (3200, (300, 4096, 8200))])
 @pytest.mark.parametrize("general", [False, True])
-def test_gptq_rows_do_not_depend_on_row_count(general):
+def test_gptq_rows_do_not_depend_on_row_count(n, rows, general):
     """The rows are independent, so a row's results are the same bits whichever
-    kernel its layer's row count picks: all errors in LDS (300 and 12300 rows: 19
-    and 769 workgroups) or the older ones from memory (8200 and 16400 rows: 513 and
-    1025).  35 column tiles: older errors, two ranges, a push."""
+    kernels its layer's row count picks: all errors in LDS (300, 4096 and 12300 rows:
+    19, 256 and 769 workgroups) or the older ones from memory (8200 and 16400 rows: 513
+    and 1025); range pushes in 64 x 64 (300 rows), 128 x 128 (4096 x 3200) or 256 x 256
+    blocks (8200 x 3200)."""
     import torch
     import paper_2608_06291_amd as pk
-    n = 1100
     p = _problem(16, n, seed=66)
     rng = np.random.default_rng(67)
-    W = torch.from_numpy((0.02 * rng.standard_normal((16400, n))).astype(np.float32)).to("cuda:0")
+    W = torch.from_numpy((0.02 * rng.standard_normal((rows[-1], n))).astype(np.float32)).to("cuda:0")
     f = pk.factor(torch.from_numpy(p["A"]).to("cuda:0"), None, p["damp"])
     kw, groups = {}, 1
     if general:
         groups = -(-n // 100)
         kw = dict(alphabet="asym", group_size=100,
                   col_scale=torch.from_numpy(rng.uniform(0.8, 1.25, n).astype(np.float32)).to("cuda:0"))
-    scale = torch.from_numpy(rng.uniform(0.005, 0.01, (16400, groups)).astype(np.float32)).to("cuda:0")
+    scale = torch.from_numpy(rng.uniform(0.005, 0.01, (rows[-1], groups)).astype(np.float32)).to("cuda:0")
     ref = None
-    for m in (300, 8200, 12300, 16400):
-        log(f"case one-sided rows m={m} general={general}")
+    for m in rows:
+        log(f"case one-sided rows m={m} n={n} general={general}")
         out = [t[:300].cpu().numpy() for t in
                pk.solve(W[:m], f, 4, scale[:m].reshape(-1).contiguous(), debug=True, **kw)[:3]]
         if ref is None:

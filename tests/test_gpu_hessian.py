@@ -76,8 +76,8 @@ def test_gram_parity(oracle_mod, N, d, weighted, masked):
 @pytest.mark.parametrize("N,d", [(15, 127), (16, 128), (17, 129), (20, 255), (35, 256), (5000, 257),
                                  (9000, 515), (3, 2)])
 def test_gram_and_quadform_block_edges(oracle_mod, N, d):
-    """Chunk (16 samples), block (128 and 256) and matrix-end remainders, rows at
-    every 4-byte alignment, both block sizes; and an infinite entry makes its own
+    """Chunk (16 samples), block (128) and matrix-end remainders, rows at every 4-byte
+    alignment (128-wide blocks; the wide ones below); and an infinite entry makes its own
     row and column non-finite and leaves the others as they are."""
     import torch
     import paper_2608_06291_amd as pk
@@ -152,7 +152,7 @@ def test_short_sums(N):
 def test_gram_and_quadform_infinities(N, d):
     """Infinite entries and products that overflow give what fp32 arithmetic gives
     (infinite where the sum is, NaN for opposite infinities), and the entries
-    without them keep their bits; both block edges."""
+    without them keep their bits (128-wide blocks; the wide ones below)."""
     import torch
     import paper_2608_06291_amd as pk
     log(f"case infinities N={N} d={d}")
@@ -191,6 +191,64 @@ def test_gram_and_quadform_infinities(N, d):
     keep = np.ones(N, bool)
     keep[[3, 60]] = False
     assert np.isfinite(w0).all() and np.array_equal(w[keep], w0[keep])
+
+
+@pytest.mark.parametrize("N,d", [(703, 2999), (1501, 2299), (3001, 2047)])
+def test_gram_wide_blocks(N, d):
+    """Sizes for which the Gram takes 256-wide blocks (told by the workspace size),
+    with remainders of samples and features, weights, rows off 16-byte alignment:
+    within the fp32 summation bound, N + 1 roundings (the weight), and symmetric; an
+    infinite entry gives its row and column what fp32 arithmetic gives and leaves the
+    bits of the others."""
+    import torch
+    import paper_2608_06291_amd as pk
+    log(f"case wide Gram N={N} d={d}")
+    nb = -(-d // 256)
+    assert pk.gram_workspace_bytes(N, d) % (nb * (nb + 1) // 2 * 256 * 256 * 4) == 0
+    r = np.random.Generator(np.random.PCG64(np.random.SeedSequence([4023, N])))
+    X = r.standard_normal((N, d)).astype(np.float32)
+    w = r.uniform(0.5, 2.0, N).astype(np.float32)
+    flat = torch.empty(N * d + 1, device="cuda:0")
+    Xd = flat[1:].view(N, d)
+    Xd.copy_(_dev(X))
+    C = pk.gram(Xd, _dev(w), 1.0).cpu().numpy()
+    X64 = X.astype(np.float64)
+    ref, abssum = (X64 * w[:, None]).T @ X64, (np.abs(X64) * w[:, None]).T @ np.abs(X64)
+    err = np.abs(C - ref) / abssum
+    log(f"[wide gram {N}x{d}] max {np.max(err) / U32:.2f} u rms {np.sqrt(np.mean(err ** 2)) / U32:.3f} u")
+    assert np.max(err) <= (N + 1) * U32
+    # rms: 16 k's share a rounding per partial product, so well below one half ulp
+    assert np.sqrt(np.mean(err ** 2)) <= 0.5 * U32
+    assert np.array_equal(C, C.T)
+    Xd[N - 1, d - 1] = float("inf")
+    Ci = pk.gram(Xd, _dev(w), 1.0).cpu().numpy()
+    assert np.array_equal(Ci[:d - 1, :d - 1], C[:d - 1, :d - 1])
+    assert np.array_equal(Ci[d - 1, :d - 1], np.where(X[N - 1, :d - 1] > 0, np.inf, -np.inf).astype(np.float32))
+    assert Ci[d - 1, d - 1] == np.inf
+
+
+def test_quadform_wide_blocks():
+    """A size for which the quadratic form takes 256-wide blocks on 256 CUs (79 x 5
+    blocks), with remainders: within (2 d + 8) u, and an infinite sample gives an
+    infinite form and leaves the bits of the others."""
+    import torch
+    import paper_2608_06291_amd as pk
+    N, d = 20011, 1031
+    log(f"case wide quadratic form N={N} d={d}")
+    r = np.random.Generator(np.random.PCG64(np.random.SeedSequence([4024])))
+    X = np.abs(r.standard_normal((N, d))).astype(np.float32)
+    Z = r.random((d, 3))
+    M = (Z @ Z.T).astype(np.float32)
+    flat = torch.empty(N * d + 1, device="cuda:0")
+    Xd = flat[1:].view(N, d)
+    Xd.copy_(_dev(X))
+    w = pk.quadform_weights(Xd, _dev(M)).cpu().numpy()
+    X64 = X.astype(np.float64)
+    ref = np.sum((X64 @ M.astype(np.float64)) * X64, axis=1)   # all terms positive
+    assert np.max(np.abs(w - ref) / ref) <= (2 * d + 8) * U32
+    Xd[N - 1, d - 1] = float("inf")
+    wi = pk.quadform_weights(Xd, _dev(M)).cpu().numpy()
+    assert wi[N - 1] == np.inf and np.array_equal(wi[:-1], w[:-1])
 
 
 def test_gram_in_place_mask_empty_and_deterministic(oracle_mod):
