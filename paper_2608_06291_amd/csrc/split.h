@@ -18,8 +18,12 @@
 // v_mfma_f32_32x32x2f32, so from 3 or 4 terms on a sum is nearer to its 64-bit
 // value than with fp32 MFMA: rms against sum |a b| over 1, 2, 4, 16, 2000 terms 0.57,
 // 0.47, 0.36, 0.21, 0.10 u here and 0.43, 0.44, 0.45, 0.48, 0.13 u there (normal
-// operands).  With h truncated instead of rounded, at the same cost, the part left
-// out is four times as large (single products up to 5.4 u).
+// operands).  With h truncated instead of rounded, the same number of operations, the
+// part left out is four times as large (single products up to 5.4 u); the launches at
+// the power limit are then a little quicker (28672 x 8192 solve 65.8 ms, 66.8 with
+// rounding), as the signs of m and l vary less.  Rounding in one operand only, told
+// apart by the wave, makes the pushes of 64 x 64 and 128 x 128 blocks slower (one-sided
+// 4096 x 4096 2%).
 // Range: the split is exact for |x| >= 2^-110; below, l falls under bf16's
 // smallest number and x is kept to within 2^-133.  An operand that is not finite,
 // or above 2^128 - 2^119 (h rounds to infinity), makes the products it enters NaN.
